@@ -18,6 +18,7 @@
 namespace {
 thread_local std::string g_err;
 constexpr size_t kRingBytes = (size_t)8 << 20;
+constexpr size_t kHostResultBytes = 4096;
 constexpr int kMaxPartials = 4096;
 }  // namespace
 
@@ -226,6 +227,8 @@ void release(qs_state *st)
     for (int c = 0; c < kRingChunks; ++c)
         if (st->ring_ev[c])
             (void)hipEventDestroy(st->ring_ev[c]);
+    if (st->hresult_ev)
+        (void)hipEventDestroy(st->hresult_ev);
     if (st->hring)
         (void)hipHostFree(st->hring);
     if (st->dring)
@@ -572,10 +575,17 @@ QS_API int qs_alloc(qs_state **out, int n, int dtype, void *dev_buf, void *hip_s
         st->owns = true;
     }
     st->ring_bytes = kRingBytes;
-    e = hipHostMalloc((void **)&st->hring, kRingBytes, hipHostMallocDefault);
+    e = hipHostMalloc((void **)&st->hring, kRingBytes + kHostResultBytes, hipHostMallocDefault);
     if (e != hipSuccess) {
         st->hring = nullptr;
         rc = qs_hip_fail(e, "hipHostMalloc(staging ring)");
+        goto fail;
+    }
+    st->hresult = reinterpret_cast<double *>(st->hring + kRingBytes);
+    e = hipEventCreateWithFlags(&st->hresult_ev, hipEventDisableTiming);
+    if (e != hipSuccess) {
+        st->hresult_ev = nullptr;
+        rc = qs_hip_fail(e, "hipEventCreate");
         goto fail;
     }
     e = hipMalloc((void **)&st->dring, kRingBytes);

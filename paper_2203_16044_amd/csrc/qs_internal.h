@@ -44,9 +44,13 @@ struct qs_state {
     size_t ring_head = 0;
     hipEvent_t ring_ev[kRingChunks] = {};
     bool ring_ev_live[kRingChunks] = {};
-    // FP64 reduction scratch: per-block partial sums followed by the result slot and the pending-norm slot
+    // FP64 reduction scratch: per-block partial sums followed by the result slot, the pending-norm slot and a
+    // measurement's result
     double *red = nullptr;
     size_t red_cap = 0;
+    // pinned host slot a kernel writes results to, and the event that says it has
+    double *hresult = nullptr;
+    hipEvent_t hresult_ev = nullptr;
     // per-workgroup partial sums of a norm folded into a block pass (allocated on first use)
     double *blkred = nullptr;
     size_t blkred_cap = 0;

@@ -2,8 +2,8 @@
 // vector gives the outcome probabilities directly, and a measured state collapses onto the observed outcome).
 //
 //  * qs_measure: one FP64 pass yields P0 and P1 (the probability mass with the qubit's bit 0 / 1), the outcome is
-//    decided on the host in FP64 from a caller-supplied uniform u, and one more pass keeps the amplitudes of the
-//    observed outcome, scaled by 1/sqrt(P_outcome), and zeroes the others.
+//    decided in FP64 from a caller-supplied uniform u, and one more pass keeps the amplitudes of the observed outcome,
+//    scaled by 1/sqrt(P_outcome), and zeroes the others.
 //  * qs_sample: the state is cut into chunks of 4096 amplitudes (one wave each: 64 lanes x 64 consecutive
 //    amplitudes); each chunk's FP64 mass is the last element of a wave-inclusive scan of its lane sums, a
 //    deterministic two-level scan turns the chunk masses into an inclusive prefix, and each shot (one wave)
@@ -30,20 +30,55 @@ __device__ __forceinline__ double mag2(const typename MT<R>::C2 &v)
     return re * re + im * im;
 }
 
-// Per-block FP64 masses of the amplitudes whose bit q is 0 and 1 (grid-stride, then an LDS tree in fixed order).
+// 16-byte vector v of a state holds P amplitudes from index P v on (P = 1 complex128, 2 complex64). Whether an
+// amplitude's bit q is set depends on the vector alone, except for complex64, q = 0: there the vector's two halves are
+// the two outcomes.
+template <class R> struct MVec;
+template <> struct MVec<double> { typedef double T __attribute__((ext_vector_type(2))); };
+template <> struct MVec<float> { typedef float T __attribute__((ext_vector_type(4))); };
+
+// Per-block FP64 masses of the amplitudes whose bit q is 0 and 1 (grid-stride over 16-byte vectors, four loads in
+// flight per thread, then an LDS tree in fixed order).
 template <class R>
-__global__ __launch_bounds__(256) void k_measure_partials(const typename MT<R>::C2 *__restrict__ psi, uint64_t dim,
+__global__ __launch_bounds__(256) void k_measure_partials(const typename MVec<R>::T *__restrict__ psi, uint64_t nvec,
                                                           int q, double *__restrict__ partials)
 {
+    using V = typename MVec<R>::T;
+    constexpr int U = 4;
     __shared__ double r0[256], r1[256];
     double a0 = 0.0, a1 = 0.0;
-    for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < dim; i += (uint64_t)gridDim.x * 256) {
-        const double p = mag2<R>(psi[i]);
-        if ((i >> q) & 1)
-            a1 += p;
-        else
-            a0 += p;
+    const uint64_t stride = (uint64_t)gridDim.x * 256;
+    auto add = [&](const V &x, uint64_t v) {
+        if constexpr (sizeof(R) == 8) {
+            const double p = x.x * x.x + x.y * x.y;
+            const bool one = (v >> q) & 1;
+            a0 += one ? 0.0 : p;
+            a1 += one ? p : 0.0;
+        } else {
+            const double p = (double)x.x * (double)x.x + (double)x.y * (double)x.y;
+            const double r = (double)x.z * (double)x.z + (double)x.w * (double)x.w;
+            if (q == 0) {
+                a0 += p;
+                a1 += r;
+            } else {
+                const bool one = (v >> (q - 1)) & 1;
+                a0 += one ? 0.0 : p + r;
+                a1 += one ? p + r : 0.0;
+            }
+        }
+    };
+    uint64_t v = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    for (; v + (U - 1) * stride < nvec; v += U * stride) {
+        V x[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j)
+            x[j] = psi[v + j * stride];
+#pragma unroll
+        for (int j = 0; j < U; ++j)
+            add(x[j], v + j * stride);
     }
+    for (; v < nvec; v += stride)
+        add(psi[v], v);
     r0[threadIdx.x] = a0;
     r1[threadIdx.x] = a1;
     __syncthreads();
@@ -60,39 +95,96 @@ __global__ __launch_bounds__(256) void k_measure_partials(const typename MT<R>::
     }
 }
 
-// Sum the partial pairs in a fixed order (compensated), result[0] = P0, result[1] = P1.
-__global__ __launch_bounds__(64) void k_measure_total(const double *__restrict__ partials, int nb,
-                                                      double *__restrict__ result)
+// s + c <- (s + c) + v, the rounding error of s + v kept in c (Knuth's two-sum).
+__device__ __forceinline__ void two_sum(double &s, double &c, double v)
 {
-    if (threadIdx.x >= 2)
-        return;
-    double s = 0.0, c = 0.0;
-    for (int b = 0; b < nb; ++b) {
-        const double y = partials[2 * b + threadIdx.x] - c;
-        const double t = s + y;
-        c = (t - s) - y;
-        s = t;
-    }
-    result[threadIdx.x] = s;
+    const double t = s + v;
+    const double z = t - s;
+    c += (s - (t - z)) + (v - z);
+    s = t;
 }
 
-// Keep the amplitudes whose bit q equals `outcome`, scaled by `scale` in FP64; zero the others (not read).
-template <class R>
-__global__ __launch_bounds__(256) void k_collapse(typename MT<R>::C2 *__restrict__ psi, uint64_t dim, int q,
-                                                  int outcome, double scale)
+// What a measurement decided (device memory; P0 and P1 also go to the host).
+struct MeasResult {
+    double P0, P1;
+    double scale;  // 1 / sqrt(mass of the outcome)
+    int outcome;   // 0 or 1; -1: the state has no finite nonzero mass (it is then left as it is)
+};
+
+// Sum the partial pairs in a fixed order (compensated: each of 128 threads per outcome its share, then a tree) and
+// decide the outcome: 1 iff u (P0 + P1) < P1. One workgroup; what bounds it is the latency of one round of loads and
+// of seven tree steps, then the write to the host (2,048 pairs: 6 us; one thread per outcome walking all of them in
+// sequence took 209 us).
+__global__ __launch_bounds__(256) void k_measure_decide(const double *__restrict__ partials, int nb, double u,
+                                                        MeasResult *__restrict__ result, double *__restrict__ host)
 {
-    using C2 = typename MT<R>::C2;
-    for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < dim; i += (uint64_t)gridDim.x * 256) {
-        C2 v;
-        if ((int)((i >> q) & 1) == outcome) {
-            v = psi[i];
-            v.x = (R)((double)v.x * scale);
-            v.y = (R)((double)v.y * scale);
-        } else {
-            v.x = 0;
-            v.y = 0;
+    __shared__ double ss[256], sc[256];
+    const int t = threadIdx.x, o = t & 1;
+    double s = 0.0, c = 0.0;
+    for (int b = t >> 1; b < nb; b += 128)
+        two_sum(s, c, partials[2 * b + o]);
+    ss[t] = s;
+    sc[t] = c;
+    __syncthreads();
+    for (int w = 128; w > 1; w >>= 1) {  // t and t + w hold the same outcome
+        if (t < w) {
+            two_sum(s, c, ss[t + w]);
+            c += sc[t + w];
+            ss[t] = s;
+            sc[t] = c;
         }
-        psi[i] = v;
+        __syncthreads();
+    }
+    if (t == 0) {
+        const double P0 = ss[0] + sc[0], P1 = ss[1] + sc[1], tot = P0 + P1;
+        const bool ok = tot > 0.0 && tot <= 1.7976931348623157e308;
+        const int out = u * tot < P1 ? 1 : 0;
+        result->P0 = P0;
+        result->P1 = P1;
+        result->scale = 1.0 / sqrt(out ? P1 : P0);
+        result->outcome = ok ? out : -1;
+        host[0] = P0;
+        host[1] = P1;
+    }
+}
+
+// Keep the amplitudes of the observed outcome, scaled in FP64; zero the others (not read, but for complex64, q = 0,
+// where both outcomes share each vector).
+template <class R>
+__global__ __launch_bounds__(256) void k_collapse(typename MVec<R>::T *__restrict__ psi, uint64_t nvec, int q,
+                                                  const MeasResult *__restrict__ result)
+{
+    using V = typename MVec<R>::T;
+    const int outcome = result->outcome;
+    if (outcome < 0)
+        return;
+    const double scale = result->scale;
+    for (uint64_t v = (uint64_t)blockIdx.x * 256 + threadIdx.x; v < nvec; v += (uint64_t)gridDim.x * 256) {
+        V x;
+        if constexpr (sizeof(R) == 8) {
+            x = V{0, 0};
+            if ((int)((v >> q) & 1) == outcome) {
+                x = psi[v];
+                x.x *= scale;
+                x.y *= scale;
+            }
+        } else {
+            x = V{0, 0, 0, 0};
+            if (q == 0 || (int)((v >> (q - 1)) & 1) == outcome) {
+                x = psi[v];
+                x.x = (R)((double)x.x * scale);
+                x.y = (R)((double)x.y * scale);
+                x.z = (R)((double)x.z * scale);
+                x.w = (R)((double)x.w * scale);
+                if (q == 0) {
+                    if (outcome)
+                        x.x = x.y = 0;
+                    else
+                        x.z = x.w = 0;
+                }
+            }
+        }
+        psi[v] = x;
     }
 }
 
@@ -261,28 +353,27 @@ __global__ __launch_bounds__(256) void k_sample(const typename MT<R>::C2 *__rest
 }
 
 template <class R>
-hipError_t measure_r(void *psi, uint64_t dim, int q, double *partials, double *result, hipStream_t s)
+hipError_t measure_r(void *psi, uint64_t dim, int q, double u, double *partials, MeasResult *result, double *host,
+                     hipEvent_t decided, hipStream_t s)
 {
-    using C2 = typename MT<R>::C2;
+    using V = typename MVec<R>::T;
+    const uint64_t nvec = sizeof(R) == 8 ? dim : dim / 2;
     uint64_t nb = (dim + 256 * 16 - 1) / (256 * 16);
     if (nb > (uint64_t)kMeasBlocks)
         nb = kMeasBlocks;
-    if (nb == 0)
-        nb = 1;
-    hipLaunchKernelGGL((k_measure_partials<R>), dim3((unsigned)nb), dim3(256), 0, s, (const C2 *)psi, dim, q,
+    hipLaunchKernelGGL((k_measure_partials<R>), dim3((unsigned)nb), dim3(256), 0, s, (const V *)psi, nvec, q,
                        partials);
-    hipLaunchKernelGGL(k_measure_total, dim3(1), dim3(64), 0, s, (const double *)partials, (int)nb, result);
-    return hipGetLastError();
-}
-
-template <class R>
-hipError_t collapse_r(void *psi, uint64_t dim, int q, int outcome, double scale, hipStream_t s)
-{
-    using C2 = typename MT<R>::C2;
-    uint64_t grid = (dim + 255) / 256;
+    hipLaunchKernelGGL(k_measure_decide, dim3(1), dim3(256), 0, s, (const double *)partials, (int)nb, u, result, host);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess)
+        e = hipEventRecord(decided, s);
+    if (e != hipSuccess)
+        return e;
+    uint64_t grid = (nvec + 255) / 256;
     if (grid > ((uint64_t)1 << 20))
         grid = (uint64_t)1 << 20;
-    hipLaunchKernelGGL((k_collapse<R>), dim3((unsigned)grid), dim3(256), 0, s, (C2 *)psi, dim, q, outcome, scale);
+    hipLaunchKernelGGL((k_collapse<R>), dim3((unsigned)grid), dim3(256), 0, s, (V *)psi, nvec, q,
+                       (const MeasResult *)result);
     return hipGetLastError();
 }
 
@@ -318,27 +409,25 @@ hipError_t sample_r(const void *psi, uint64_t dim, const SampleGeom &g, double *
     return hipGetLastError();
 }
 
+// The collapse is enqueued behind the decision, which the GPU takes itself; the host waits for the decision alone and
+// is free to enqueue what follows while the collapse runs.
 int measure_impl(qs_state *st, int qubit, double u, int *outcome, double *prob_one)
 {
     const uint64_t dim = (uint64_t)1 << st->n;
     double *partials = st->red;
-    double *result = st->red + 2 * kMeasBlocks;
-    QS_HIP(st->dtype == QS_C128 ? measure_r<double>(st->psi, dim, qubit, partials, result, st->stream)
-                                : measure_r<float>(st->psi, dim, qubit, partials, result, st->stream));
-    double P[2] = {0.0, 0.0};
-    QS_HIP(hipMemcpyAsync(P, result, sizeof(P), hipMemcpyDeviceToHost, st->stream));
-    QS_HIP(hipStreamSynchronize(st->stream));
-    const double tot = P[0] + P[1];
+    MeasResult *result = reinterpret_cast<MeasResult *>(st->red + 2 * kMeasBlocks + 4);
+    QS_HIP(st->dtype == QS_C128 ? measure_r<double>(st->psi, dim, qubit, u, partials, result, st->hresult,
+                                                    st->hresult_ev, st->stream)
+                                : measure_r<float>(st->psi, dim, qubit, u, partials, result, st->hresult,
+                                                   st->hresult_ev, st->stream));
+    QS_HIP(hipEventSynchronize(st->hresult_ev));
+    const double P0 = st->hresult[0], P1 = st->hresult[1], tot = P0 + P1;
     if (!(tot > 0.0) || !std::isfinite(tot))
         return qs_fail(QS_EINVAL, "qs_measure: the state has no finite nonzero mass (%g)", tot);
-    const int out = (u * tot < P[1]) ? 1 : 0;
-    const double keep = out ? P[1] : P[0];
-    QS_HIP(st->dtype == QS_C128 ? collapse_r<double>(st->psi, dim, qubit, out, 1.0 / std::sqrt(keep), st->stream)
-                                : collapse_r<float>(st->psi, dim, qubit, out, 1.0 / std::sqrt(keep), st->stream));
     if (outcome)
-        *outcome = out;
+        *outcome = (u * tot < P1) ? 1 : 0;
     if (prob_one)
-        *prob_one = P[1] / tot;
+        *prob_one = P1 / tot;
     return QS_OK;
 }
 
@@ -355,7 +444,7 @@ QS_API int qs_measure(qs_state *st, int qubit, double u, int *outcome, double *p
         return qs_fail(QS_EINVAL, "qs_measure: qubit %d outside [0, %d)", qubit, st->n);
     if (!(u >= 0.0 && u < 1.0))
         return qs_fail(QS_EINVAL, "qs_measure: u = %g outside [0, 1)", u);
-    if (st->red_cap < 2 * (size_t)kMeasBlocks + 2)
+    if (st->red_cap < 2 * (size_t)kMeasBlocks + 8)
         return qs_fail(QS_EUNSUPPORTED, "qs_measure: reduction scratch too small");
     return measure_impl(st, qubit, u, outcome, prob_one);
 }
