@@ -193,8 +193,8 @@ QS_API int qs_measure(qs_state *st, int qubit, double u, int *outcome, double *p
 QS_API int qs_reset(qs_state *st, int qubit, double u, int *outcome);
 /* Draw nshots basis indices (no collapse): shot k returns the smallest i whose cumulative FP64 mass exceeds
  * u[k] x total mass (chunked deterministic prefix sums; every index returned lies in [0, 2^n)). u and out are
- * host arrays of nshots doubles / int64 (0 <= nshots <= 2^30); uses temporary device memory of about
- * 2^(n-11) doubles + 16 bytes per shot. Synchronises. QS_EINVAL for u outside [0, 1) or a state with no finite
+ * host arrays of nshots doubles / int64 (0 <= nshots <= 2^30); uses device memory of about 2^(n-11) doubles, and
+ * 16 bytes per shot from 32,769 shots on, which the state keeps for its next call when it is at most 64 MiB. Synchronises. QS_EINVAL for u outside [0, 1) or a state with no finite
  * nonzero mass. */
 QS_API int qs_sample(qs_state *st, int64_t nshots, const double *u, int64_t *out);
 

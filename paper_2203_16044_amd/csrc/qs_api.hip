@@ -47,7 +47,9 @@ extern "C" QS_API const char *qs_last_error(void) { return g_err.c_str(); }
 // staging ring: pinned host chunk -> async H2D copy on the state's stream. A host chunk is reused only after
 // the copy that last read it has completed (event per chunk); device chunk reuse is ordered by the stream.
 // ------------------------------------------------------------------------------------------------------------
-void *qs_stage(qs_state *st, const void *host, size_t bytes)
+namespace {
+// Reserve `bytes` of the ring, waiting for copies that still read them. c0..c1: the chunks they lie in.
+char *ring_reserve(qs_state *st, size_t bytes, int &c0, int &c1)
 {
     const size_t need = (bytes + 255) & ~(size_t)255;
     if (need > st->ring_bytes) {
@@ -57,7 +59,8 @@ void *qs_stage(qs_state *st, const void *host, size_t bytes)
     if (st->ring_head + need > st->ring_bytes)
         st->ring_head = 0;
     const size_t csz = st->ring_bytes / kRingChunks;
-    const int c0 = (int)(st->ring_head / csz), c1 = (int)((st->ring_head + need - 1) / csz);
+    c0 = (int)(st->ring_head / csz);
+    c1 = (int)((st->ring_head + need - 1) / csz);
     for (int c = c0; c <= c1; ++c) {
         if (st->ring_ev_live[c]) {
             hipError_t e = hipEventSynchronize(st->ring_ev[c]);
@@ -68,9 +71,27 @@ void *qs_stage(qs_state *st, const void *host, size_t bytes)
             st->ring_ev_live[c] = false;
         }
     }
-    std::memcpy(st->hring + st->ring_head, host, bytes);
-    hipError_t e = hipMemcpyAsync(st->dring + st->ring_head, st->hring + st->ring_head, bytes, hipMemcpyHostToDevice,
-                                  st->stream);
+    char *h = st->hring + st->ring_head;
+    st->ring_head += need;
+    return h;
+}
+}  // namespace
+
+char *qs_ring_host(qs_state *st, size_t bytes)
+{
+    int c0, c1;
+    return ring_reserve(st, bytes, c0, c1);
+}
+
+void *qs_stage(qs_state *st, const void *host, size_t bytes)
+{
+    int c0, c1;
+    char *h = ring_reserve(st, bytes, c0, c1);
+    if (!h)
+        return nullptr;
+    char *d = st->dring + (h - st->hring);
+    std::memcpy(h, host, bytes);
+    hipError_t e = hipMemcpyAsync(d, h, bytes, hipMemcpyHostToDevice, st->stream);
     if (e != hipSuccess) {
         qs_hip_fail(e, "hipMemcpyAsync(staging ring)");
         return nullptr;
@@ -83,9 +104,33 @@ void *qs_stage(qs_state *st, const void *host, size_t bytes)
         }
         st->ring_ev_live[c] = true;
     }
-    void *d = st->dring + st->ring_head;
-    st->ring_head += need;
     return d;
+}
+
+char *qs_scratch(qs_state *st, size_t bytes)
+{
+    if (bytes <= st->scratch_cap)
+        return st->scratch;
+    qs_scratch_drop(st);
+    const size_t cap = (bytes + 4095) & ~(size_t)4095;
+    hipError_t e = hipMalloc((void **)&st->scratch, cap);
+    if (e != hipSuccess) {
+        st->scratch = nullptr;
+        qs_hip_fail(e, "hipMalloc(scratch)");
+        return nullptr;
+    }
+    st->scratch_cap = cap;
+    return st->scratch;
+}
+
+void qs_scratch_drop(qs_state *st)
+{
+    if (!st->scratch)
+        return;
+    (void)hipStreamSynchronize(st->stream);  // queued work may still use it
+    (void)hipFree(st->scratch);
+    st->scratch = nullptr;
+    st->scratch_cap = 0;
 }
 
 // ---- device properties and kernel attributes, shared by the launchers ----
@@ -237,6 +282,8 @@ void release(qs_state *st)
         (void)hipFree(st->red);
     if (st->blkred)
         (void)hipFree(st->blkred);
+    if (st->scratch)
+        (void)hipFree(st->scratch);
     if (st->owns && st->psi)
         (void)hipFree(st->psi);
     delete st;

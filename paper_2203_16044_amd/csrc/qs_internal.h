@@ -54,6 +54,9 @@ struct qs_state {
     // per-workgroup partial sums of a norm folded into a block pass (allocated on first use)
     double *blkred = nullptr;
     size_t blkred_cap = 0;
+    // sampling scratch (qs_scratch)
+    char *scratch = nullptr;
+    size_t scratch_cap = 0;
 };
 // device slot holding the norm a folded renormalisation computed last (qs_plan_run_renorm)
 double *qs_pending_norm(qs_state *st);
@@ -64,6 +67,13 @@ double *qs_block_partials(qs_state *st, size_t n);
 // Copy `bytes` of host data to the device through the staging ring (async on st->stream). Returns the device
 // address, or nullptr on failure (error already recorded).
 void *qs_stage(qs_state *st, const void *host, size_t bytes);
+// `bytes` of the ring's pinned host memory that no copy still reads, for a caller that waits for its use of them before
+// it returns (nullptr and the error recorded on failure).
+char *qs_ring_host(qs_state *st, size_t bytes);
+// Device scratch of at least `bytes` that the state keeps until qs_scratch_drop or its end (nullptr and the error
+// recorded on failure); ordered by the state's stream.
+char *qs_scratch(qs_state *st, size_t bytes);
+void qs_scratch_drop(qs_state *st);
 
 inline size_t amp_bytes(int dtype) { return dtype == QS_C128 ? 16 : 8; }
 

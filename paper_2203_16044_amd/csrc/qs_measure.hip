@@ -4,31 +4,23 @@
 //  * qs_measure: one FP64 pass yields P0 and P1 (the probability mass with the qubit's bit 0 / 1), the outcome is
 //    decided in FP64 from a caller-supplied uniform u, and one more pass keeps the amplitudes of the observed outcome,
 //    scaled by 1/sqrt(P_outcome), and zeroes the others.
-//  * qs_sample: the state is cut into chunks of 4096 amplitudes (one wave each: 64 lanes x 64 consecutive
-//    amplitudes); each chunk's FP64 mass is the last element of a wave-inclusive scan of its lane sums, a
-//    deterministic two-level scan turns the chunk masses into an inclusive prefix, and each shot (one wave)
-//    finds its chunk by binary search and its index by repeating the chunk's scan. Shot k returns the smallest
-//    index i whose cumulative mass exceeds u_k x total mass, with the same additions on every path.
+//  * qs_sample: the state is cut into chunks of 2048 amplitudes (one wave each); each chunk's FP64 mass is reduced
+//    from coalesced loads, a deterministic two-level scan turns the chunk masses into an inclusive prefix, and each
+//    shot (one wave) finds its chunk by a 64-ary search and its index by two wave scans over the chunk's probabilities
+//    held in LDS. Shot k returns the smallest index i whose cumulative mass exceeds u_k x total mass, up to the
+//    rounding of the sums; an index without mass is never returned.
 #include <cmath>
+#include <cstring>
 
 #include "qs_internal.h"
 
 namespace {
 
-template <class R> struct MT;
-template <> struct MT<double> { using C2 = double2; };
-template <> struct MT<float> { using C2 = float2; };
-
 constexpr int kMeasBlocks = 2048;  // partial pairs fit the state's reduction scratch (2 x 2048 <= 4096)
-constexpr int kChunkLog = 12;      // 4096 amplitudes per sampling chunk
+constexpr int kChunkLog = 11;      // 2048 amplitudes per sampling chunk
 constexpr int kTile = 2048;        // chunk masses scanned per workgroup (256 threads x 8)
-
-template <class R>
-__device__ __forceinline__ double mag2(const typename MT<R>::C2 &v)
-{
-    const double re = (double)v.x, im = (double)v.y;
-    return re * re + im * im;
-}
+constexpr size_t kSampleKeep = (size_t)64 << 20;  // sampling scratch a state keeps between calls
+constexpr int64_t kDirectShots = 1 << 15;  // shots whose uniforms and indices cross the bus inside the kernel
 
 // 16-byte vector v of a state holds P amplitudes from index P v on (P = 1 complex128, 2 complex64). Whether an
 // amplitude's bit q is set depends on the vector alone, except for complex64, q = 0: there the vector's two halves are
@@ -201,39 +193,55 @@ __device__ __forceinline__ double wave_incl_scan(double x)
     return x;
 }
 
-// Mass of lane `lane`'s `per` consecutive amplitudes of a chunk (sequential FP64 sum).
-template <class R>
-__device__ __forceinline__ double lane_mass(const typename MT<R>::C2 *__restrict__ psi, uint64_t first, int per,
-                                            uint64_t dim)
+// The 16-byte vectors of a chunk are read in lane order (whole lines per load), eight in flight per lane. fn(j, x) takes
+// vector j of the chunk (amplitudes P j .. P j + P - 1 of it).
+template <class R, class F>
+__device__ __forceinline__ void chunk_vectors(const typename MVec<R>::T *__restrict__ pv, int nv, F fn)
 {
-    double s = 0.0;
-    for (int j = 0; j < per; ++j) {
-        const uint64_t i = first + j;
-        if (i < dim)
-            s += mag2<R>(psi[i]);
+    using V = typename MVec<R>::T;
+    constexpr int U = 8;
+    int j = threadIdx.x & 63;
+    for (; j + (U - 1) * 64 < nv; j += U * 64) {
+        V x[U];
+#pragma unroll
+        for (int t = 0; t < U; ++t)
+            x[t] = pv[j + 64 * t];
+#pragma unroll
+        for (int t = 0; t < U; ++t)
+            fn(j + 64 * t, x[t]);
     }
-    return s;
+    for (; j < nv; j += 64)
+        fn(j, pv[j]);
 }
 
-// One wave per chunk: its mass = the last element of the wave-inclusive scan of the lane masses.
+// One wave per chunk: its mass, each lane's share summed in order, then a butterfly over the lanes. Bound by the read
+// of the state: 27 qubits complex128 (2 GiB) 0.366 ms = 5.9 TB/s, against 2.24 ms with 64 consecutive amplitudes per
+// lane (every load instruction of a wave touched 64 lines).
 template <class R>
-__global__ __launch_bounds__(256) void k_chunk_mass(const typename MT<R>::C2 *__restrict__ psi, uint64_t dim,
-                                                    uint64_t chunk, int per, uint64_t nchunks,
-                                                    double *__restrict__ mass)
+__global__ __launch_bounds__(256) void k_chunk_mass(const typename MVec<R>::T *__restrict__ psi, int nv,
+                                                    uint64_t nchunks, double *__restrict__ mass)
 {
+    using V = typename MVec<R>::T;
     const uint64_t c = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (c >= nchunks)
         return;  // whole waves leave together
-    const int lane = threadIdx.x & 63;
-    const double incl = wave_incl_scan(lane_mass<R>(psi, c * chunk + (uint64_t)lane * per, per, dim));
-    if (lane == 63)
-        mass[c] = incl;
+    double s = 0.0;
+    chunk_vectors<R>(psi + c * (uint64_t)nv, nv, [&](int, const V &x) {
+        s += (double)x.x * (double)x.x + (double)x.y * (double)x.y;
+        if constexpr (sizeof(R) == 4)
+            s += (double)x.z * (double)x.z + (double)x.w * (double)x.w;
+    });
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1)
+        s += __shfl_xor(s, d, 64);
+    if ((threadIdx.x & 63) == 0)
+        mass[c] = s;
 }
 
 // Level 1 of the prefix scan: each workgroup scans a tile of kTile masses (8 sequential per thread, then an LDS
-// Hillis-Steele scan of the 256 thread sums) into tile-local inclusive prefixes, and writes the tile total.
-__global__ __launch_bounds__(256) void k_scan_tile(const double *__restrict__ in, uint64_t len,
-                                                   double *__restrict__ out, double *__restrict__ totals)
+// Hillis-Steele scan of the 256 thread sums) into tile-local inclusive prefixes, in place, and writes the tile total.
+__global__ __launch_bounds__(256) void k_scan_tile(double *__restrict__ io, uint64_t len,
+                                                   double *__restrict__ totals)
 {
     __shared__ double sh[256];
     const uint64_t base = (uint64_t)blockIdx.x * kTile + (uint64_t)threadIdx.x * 8;
@@ -241,7 +249,7 @@ __global__ __launch_bounds__(256) void k_scan_tile(const double *__restrict__ in
     double run = 0.0;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        v[j] = base + j < len ? in[base + j] : 0.0;
+        v[j] = base + j < len ? io[base + j] : 0.0;
         run += v[j];
         v[j] = run;
     }
@@ -257,23 +265,41 @@ __global__ __launch_bounds__(256) void k_scan_tile(const double *__restrict__ in
 #pragma unroll
     for (int j = 0; j < 8; ++j)
         if (base + j < len)
-            out[base + j] = before + v[j];
+            io[base + j] = before + v[j];
     if (threadIdx.x == 255)
         totals[blockIdx.x] = sh[255];
 }
 
-// Level 2: one thread turns the tile totals into exclusive tile offsets (sequential order).
-__global__ void k_scan_totals(double *__restrict__ totals, uint64_t ntiles)
+// Level 2: the tile totals become exclusive tile offsets, totals[ntiles] their sum. The additions run in sequence (so
+// that a tile's offset is bit for bit the last prefix of the tile before it and the prefix never falls); what is
+// parallel is the traffic: 2048 totals at a time pass through LDS.
+__global__ __launch_bounds__(256) void k_scan_totals(double *__restrict__ totals, uint64_t ntiles)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0)
-        return;
-    double run = 0.0;
-    for (uint64_t t = 0; t < ntiles; ++t) {
-        const double x = totals[t];
-        totals[t] = run;
-        run += x;
+    __shared__ double sh[2048];
+    __shared__ double carry;
+    if (threadIdx.x == 0)
+        carry = 0.0;
+    for (uint64_t t0 = 0; t0 < ntiles; t0 += 2048) {
+        const int cnt = (int)(ntiles - t0 < 2048 ? ntiles - t0 : 2048);
+        for (int i = threadIdx.x; i < cnt; i += 256)
+            sh[i] = totals[t0 + i];
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double run = carry;
+            for (int i = 0; i < cnt; ++i) {
+                const double x = sh[i];
+                sh[i] = run;
+                run += x;
+            }
+            carry = run;
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; i < cnt; i += 256)
+            totals[t0 + i] = sh[i];
+        __syncthreads();
     }
-    totals[ntiles] = run;
+    if (threadIdx.x == 0)
+        totals[ntiles] = carry;
 }
 
 // Level 3: add each tile's offset.
@@ -285,71 +311,75 @@ __global__ __launch_bounds__(256) void k_scan_add(double *__restrict__ out, uint
         out[i] += offs[i / kTile];
 }
 
-// One wave per shot. total = incl[last]; target = u x total; the chunk is the smallest c with incl[c] > target
-// (or, when rounding puts the target at the total, the smallest c with incl[c] >= total); the index is found by
-// repeating the chunk's lane sums and wave scan. If rounding leaves no index above the residual, the chunk's last
-// index with nonzero mass is taken. Every returned index lies in [0, dim).
+// One wave per shot, one wave per workgroup (16.5 KB of LDS). total = incl[last]; target = u x total; the chunk is the
+// smallest c with incl[c] > target (or, when rounding puts the target at the total, the smallest c with
+// incl[c] >= total), found by a 64-ary search: three rounds of loads for 2^18 chunks where a binary search waits for
+// eighteen. The chunk's probabilities go to LDS (kept when the wave's next shot falls into the same chunk); lane l sums
+// the chunk/64 consecutive ones of sub-block l, a wave scan of the sums finds the sub-block, a wave scan of its
+// elements the index. If rounding leaves no index above the residual, the last index with nonzero mass is taken. Every
+// returned index lies in [0, dim) and, where the state has any mass, has mass. Bound by the search's and the chunk's
+// load latency: 4,096 shots at 27 qubits 33 us (153 us with a binary search and strided loads).
 template <class R>
-__global__ __launch_bounds__(256) void k_sample(const typename MT<R>::C2 *__restrict__ psi, uint64_t dim,
-                                                uint64_t chunk, int per, uint64_t nchunks,
-                                                const double *__restrict__ incl, const double *__restrict__ u,
-                                                int64_t nshots,
-                                                int64_t *__restrict__ out)
+__global__ __launch_bounds__(64) void k_sample(const typename MVec<R>::T *__restrict__ psi, int chunk, int nv, int per,
+                                               uint64_t nchunks, const double *__restrict__ incl,
+                                               const double *__restrict__ u, int64_t nshots, int64_t *__restrict__ out,
+                                               double *__restrict__ total_out)
 {
-    const int64_t shot = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (shot >= nshots)
-        return;
-    const int lane = threadIdx.x & 63;
+    using V = typename MVec<R>::T;
+    constexpr int P = sizeof(R) == 8 ? 1 : 2;
+    __shared__ double p[(1 << kChunkLog) + (1 << kChunkLog) / 32];  // element i at i + i / 32: lanes on distinct banks
+    auto at = [](int i) { return i + (i >> 5); };
+    const int lane = threadIdx.x;
     const double total = incl[nchunks - 1];
-    double target = u[shot] * total;
-    const bool clamp = !(target < total);
-    uint64_t lo = 0, hi = nchunks - 1;
-    while (lo < hi) {
-        const uint64_t mid = (lo + hi) >> 1;
-        const bool right = clamp ? incl[mid] < total : incl[mid] <= target;
-        if (right)
-            lo = mid + 1;
-        else
-            hi = mid;
+    if (blockIdx.x == 0 && lane == 0)
+        *total_out = total;
+    uint64_t held = nchunks;  // the chunk in LDS
+    for (int64_t shot = blockIdx.x; shot < nshots; shot += gridDim.x) {
+        const double target = u[shot] * total;
+        const bool clamp = !(target < total);
+        uint64_t lo = 0, len = nchunks;  // the chunk is in [lo, lo + len)
+        while (len > 1) {
+            const uint64_t step = (len + 63) / 64, last = lo + len - 1;
+            const uint64_t pos = lo + (lane + 1) * step - 1;
+            const double x = incl[pos < last ? pos : last];
+            const bool right = pos < last && (clamp ? x < total : x <= target);
+            const int k = __ffsll(~__ballot(right)) - 1;  // lane 63 is never right
+            lo += k * step;
+            len = last - lo + 1 < step ? last - lo + 1 : step;
+        }
+        const uint64_t c = lo;
+        const double r = target - (c > 0 ? incl[c - 1] : 0.0);
+        if (c != held) {
+            lds_barrier();
+            chunk_vectors<R>(psi + c * (uint64_t)nv, nv, [&](int j, const V &x) {
+                p[at(P * j)] = (double)x.x * (double)x.x + (double)x.y * (double)x.y;
+                if constexpr (P == 2)
+                    p[at(P * j + 1)] = (double)x.z * (double)x.z + (double)x.w * (double)x.w;
+            });
+            lds_barrier();
+            held = c;
+        }
+        double mine = 0.0;
+        for (int j = 0; j < per; ++j)
+            if (lane * per + j < chunk)
+                mine += p[at(lane * per + j)];
+        const double sc = wave_incl_scan(mine);
+        const unsigned long long above = __ballot(!clamp && sc > r && mine > 0.0);
+        const unsigned long long nonzero = __ballot(mine > 0.0);
+        const int pick = above ? __ffsll(above) - 1 : nonzero ? 63 - __clzll(nonzero) : 0;
+        // every lane takes part in both shuffles (a lane inactive in a shuffle gives undefined values to its readers)
+        const double prev = __shfl_up(sc, 1, 64);
+        const double before = __shfl(lane > 0 ? prev : 0.0, pick, 64);
+        const double rr = r - before;
+        const int e = pick * per + lane;
+        const double x = lane < per && e < chunk ? p[at(e)] : 0.0;
+        const double acc = wave_incl_scan(x);
+        const unsigned long long hit = __ballot(above != 0 && acc > rr && x > 0.0);
+        const unsigned long long some = __ballot(x > 0.0);
+        const int sel = hit ? __ffsll(hit) - 1 : some ? 63 - __clzll(some) : 0;
+        if (lane == 0)
+            out[shot] = (int64_t)(c * (uint64_t)chunk) + pick * per + sel;
     }
-    const uint64_t c = lo;
-    const double r = target - (c > 0 ? incl[c - 1] : 0.0);
-    const uint64_t first = c * chunk + (uint64_t)lane * per;
-    const double mine = lane_mass<R>(psi, first, per, dim);
-    const double sc = wave_incl_scan(mine);
-    const unsigned long long above = __ballot(!clamp && sc > r);
-    const unsigned long long nonzero = __ballot(mine > 0.0);
-    int pick;
-    bool exact;
-    if (above) {
-        pick = __ffsll(above) - 1;
-        exact = true;
-    } else {
-        pick = nonzero ? 63 - __clzll(nonzero) : 63;
-        exact = false;
-    }
-    // every lane takes part in both shuffles (a lane inactive in a shuffle gives undefined values to its readers)
-    const double prev = __shfl_up(sc, 1, 64);
-    const double before = __shfl(lane > 0 ? prev : 0.0, pick, 64);
-    if (lane != pick)
-        return;
-    const double rr = r - (pick > 0 ? before : 0.0);
-    double acc = 0.0;
-    int64_t last_nz = -1, found = -1;
-    for (int j = 0; j < per; ++j) {
-        const uint64_t i = first + j;
-        if (i >= dim)
-            break;
-        const double p = mag2<R>(psi[i]);
-        acc += p;
-        if (p > 0.0)
-            last_nz = (int64_t)i;
-        if (exact && found < 0 && acc > rr)
-            found = (int64_t)i;
-    }
-    if (found < 0)
-        found = last_nz >= 0 ? last_nz : (int64_t)(first + per - 1 < dim ? first + per - 1 : dim - 1);
-    out[shot] = found;
 }
 
 template <class R>
@@ -393,19 +423,25 @@ SampleGeom sample_geom(uint64_t dim)
 }
 
 template <class R>
-hipError_t sample_r(const void *psi, uint64_t dim, const SampleGeom &g, double *mass, double *incl, double *tiles,
-                    const double *u, int64_t nshots, int64_t *out, hipStream_t s)
+hipError_t sample_r(const void *psi, const SampleGeom &g, double *incl, double *tiles, const double *u, int64_t nshots,
+                    int64_t *out, double *total, hipStream_t s)
 {
-    using C2 = typename MT<R>::C2;
-    hipLaunchKernelGGL((k_chunk_mass<R>), dim3((unsigned)((g.nchunks + 3) / 4)), dim3(256), 0, s, (const C2 *)psi,
-                       dim, g.chunk, g.per, g.nchunks, mass);
-    hipLaunchKernelGGL(k_scan_tile, dim3((unsigned)g.ntiles), dim3(256), 0, s, (const double *)mass, g.nchunks, incl,
-                       tiles);
-    hipLaunchKernelGGL(k_scan_totals, dim3(1), dim3(64), 0, s, tiles, g.ntiles);
-    hipLaunchKernelGGL(k_scan_add, dim3((unsigned)((g.nchunks + 255) / 256)), dim3(256), 0, s, incl, g.nchunks,
-                       (const double *)tiles);
-    hipLaunchKernelGGL((k_sample<R>), dim3((unsigned)((nshots + 3) / 4)), dim3(256), 0, s, (const C2 *)psi, dim,
-                       g.chunk, g.per, g.nchunks, (const double *)incl, u, nshots, out);
+    using V = typename MVec<R>::T;
+    const int nv = (int)(g.chunk * sizeof(R) * 2 / 16);
+    hipLaunchKernelGGL((k_chunk_mass<R>), dim3((unsigned)((g.nchunks + 3) / 4)), dim3(256), 0, s, (const V *)psi, nv,
+                       g.nchunks, incl);
+    hipLaunchKernelGGL(k_scan_tile, dim3((unsigned)g.ntiles), dim3(256), 0, s, incl, g.nchunks, tiles);
+    if (g.ntiles > 1) {  // one tile's prefixes are the whole prefix
+        hipLaunchKernelGGL(k_scan_totals, dim3(1), dim3(256), 0, s, tiles, g.ntiles);
+        hipLaunchKernelGGL(k_scan_add, dim3((unsigned)((g.nchunks + 255) / 256)), dim3(256), 0, s, incl, g.nchunks,
+                           (const double *)tiles);
+    }
+    // a wave per shot up to 64 waves per CU's worth of workgroups, then several shots per wave
+    uint64_t grid = (uint64_t)qs_cu_count() * 64;
+    if (grid > (uint64_t)nshots)
+        grid = (uint64_t)nshots;
+    hipLaunchKernelGGL((k_sample<R>), dim3((unsigned)grid), dim3(64), 0, s, (const V *)psi, (int)g.chunk, nv, g.per,
+                       g.nchunks, (const double *)incl, u, nshots, out, total);
     return hipGetLastError();
 }
 
@@ -480,31 +516,46 @@ QS_API int qs_sample(qs_state *st, int64_t nshots, const double *u, int64_t *out
         return QS_OK;
     const uint64_t dim = (uint64_t)1 << st->n;
     const SampleGeom g = sample_geom(dim);
-    // scratch: chunk masses, inclusive prefix, tile totals (+ total), uniforms, outputs
-    const size_t nd = 2 * g.nchunks + g.ntiles + 1;
-    const size_t bytes = nd * sizeof(double) + (size_t)nshots * (sizeof(double) + sizeof(int64_t));
-    char *buf = nullptr;
-    QS_HIP(hipStreamSynchronize(st->stream));
-    QS_HIP(hipMalloc(&buf, bytes));
-    double *mass = (double *)buf;
-    double *incl = mass + g.nchunks;
+    // scratch: chunk masses turned into their prefix, tile totals (+ total); for many shots also uniforms and outputs
+    const bool direct = nshots <= kDirectShots;
+    const size_t nd = g.nchunks + g.ntiles + 1;
+    const size_t bytes = (nd + 1) * sizeof(double) + (direct ? 0 : (size_t)nshots * (sizeof(double) + sizeof(int64_t)));
+    char *buf = qs_scratch(st, bytes);
+    if (!buf)
+        return QS_ENOMEM;
+    double *incl = (double *)buf;
     double *tiles = incl + g.nchunks;
-    double *du = tiles + g.ntiles + 1;
-    int64_t *dout = (int64_t *)(du + nshots);
-    hipError_t e = hipMemcpyAsync(du, u, (size_t)nshots * sizeof(double), hipMemcpyHostToDevice, st->stream);
+    const double *du = nullptr;
+    int64_t *dout = nullptr;
+    char *host = nullptr;
+    hipError_t e = hipSuccess;
+    if (direct) {  // few shots: the kernel reads the uniforms from and writes the indices to pinned host memory
+        host = qs_ring_host(st, (size_t)nshots * (sizeof(double) + sizeof(int64_t)));
+        if (!host)
+            return QS_EDEVICE;
+        std::memcpy(host, u, (size_t)nshots * sizeof(double));
+        du = (const double *)host;
+        dout = (int64_t *)(host + (size_t)nshots * sizeof(double));
+    } else {
+        double *d = tiles + g.ntiles + 2;
+        e = hipMemcpyAsync(d, u, (size_t)nshots * sizeof(double), hipMemcpyHostToDevice, st->stream);
+        du = d;
+        dout = (int64_t *)(d + nshots);
+    }
     if (e == hipSuccess)
-        e = st->dtype == QS_C128 ? sample_r<double>(st->psi, dim, g, mass, incl, tiles, du, nshots, dout, st->stream)
-                                 : sample_r<float>(st->psi, dim, g, mass, incl, tiles, du, nshots, dout, st->stream);
-    double total = 0.0;
-    if (e == hipSuccess)
+        e = st->dtype == QS_C128 ? sample_r<double>(st->psi, g, incl, tiles, du, nshots, dout, st->hresult, st->stream)
+                                 : sample_r<float>(st->psi, g, incl, tiles, du, nshots, dout, st->hresult, st->stream);
+    if (e == hipSuccess && !direct)
         e = hipMemcpyAsync(out, dout, (size_t)nshots * sizeof(int64_t), hipMemcpyDeviceToHost, st->stream);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(&total, incl + (g.nchunks - 1), sizeof(double), hipMemcpyDeviceToHost, st->stream);
-    if (e == hipSuccess)
         e = hipStreamSynchronize(st->stream);
-    (void)hipFree(buf);
+    if (bytes > kSampleKeep)
+        qs_scratch_drop(st);
     if (e != hipSuccess)
         return qs_hip_fail(e, "qs_sample");
+    const double total = st->hresult[0];
+    if (direct)
+        std::memcpy(out, host + (size_t)nshots * sizeof(double), (size_t)nshots * sizeof(int64_t));
     // a state without finite nonzero mass has no distribution: its indices are meaningless
     if (!(total > 0.0) || !std::isfinite(total))
         return qs_fail(QS_EINVAL, "qs_sample: the state has no finite nonzero mass (%g)", total);

@@ -41,6 +41,25 @@ def test_measure_edges(gpu, n, dtype):
             st.close()
 
 
+# chunks of 2048: n = 10 a part of one, 11 one, 12 two; n = 22 one scan tile, 23 two; shots 32768 / 32769: the two ways
+# uniforms and indices travel
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("n,shots,sparse", [(1, 1, False), (2, 64, False), (5, 300, True), (10, 500, False),
+                                            (11, 32769, False), (12, 32768, True), (16, 40000, True),
+                                            (22, 3000, False), (23, 3000, True)])
+def test_sample_edges(gpu, n, shots, sparse, dtype):
+    st, psi = _state(gpu, n, dtype, 200 + n, sparse)
+    u = np.random.Generator(np.random.PCG64(300 + n)).uniform(size=shots)
+    u[0] = 0.0
+    u[-1] = np.nextafter(1.0, 0.0)
+    for _ in range(2):  # the second call reuses the state's scratch
+        idx = st.sample(u)
+        assert M.samples_valid(psi, u, idx).all()
+        # an index may differ from the oracle's only where a cumulative sum ties with the target to rounding
+        assert int(np.sum(idx != M.samples(psi, u))) <= 2
+    st.close()
+
+
 def test_measure_refuses_a_state_without_finite_mass_and_leaves_it(gpu):
     for bad in (0.0, np.nan, np.inf):
         st = gpu.State(6, "c64")
@@ -48,5 +67,7 @@ def test_measure_refuses_a_state_without_finite_mass_and_leaves_it(gpu):
         st.set(psi)
         with pytest.raises(gpu.binding.QSError):
             st.measure(3, 0.5)
+        with pytest.raises(gpu.binding.QSError):
+            st.sample([0.5])
         assert st.get().tobytes() == psi.tobytes()
         st.close()
