@@ -48,8 +48,8 @@ extern "C" QS_API const char *qs_last_error(void) { return g_err.c_str(); }
 // the copy that last read it has completed (event per chunk); device chunk reuse is ordered by the stream.
 // ------------------------------------------------------------------------------------------------------------
 namespace {
-// Reserve `bytes` of the ring, waiting for copies that still read them. c0..c1: the chunks they lie in.
-char *ring_reserve(qs_state *st, size_t bytes, int &c0, int &c1)
+// Reserve `bytes` of the ring, waiting for work that still reads them. use: the chunks they lie in.
+char *ring_reserve(qs_state *st, size_t bytes, RingUse &use)
 {
     const size_t need = (bytes + 255) & ~(size_t)255;
     if (need > st->ring_bytes) {
@@ -59,9 +59,9 @@ char *ring_reserve(qs_state *st, size_t bytes, int &c0, int &c1)
     if (st->ring_head + need > st->ring_bytes)
         st->ring_head = 0;
     const size_t csz = st->ring_bytes / kRingChunks;
-    c0 = (int)(st->ring_head / csz);
-    c1 = (int)((st->ring_head + need - 1) / csz);
-    for (int c = c0; c <= c1; ++c) {
+    use.c0 = (int)(st->ring_head / csz);
+    use.c1 = (int)((st->ring_head + need - 1) / csz);
+    for (int c = use.c0; c <= use.c1; ++c) {
         if (st->ring_ev_live[c]) {
             hipError_t e = hipEventSynchronize(st->ring_ev[c]);
             if (e != hipSuccess) {
@@ -77,26 +77,24 @@ char *ring_reserve(qs_state *st, size_t bytes, int &c0, int &c1)
 }
 }  // namespace
 
-char *qs_ring_host(qs_state *st, size_t bytes)
+char *qs_ring_host(qs_state *st, size_t bytes, RingUse *use)
 {
-    int c0, c1;
-    return ring_reserve(st, bytes, c0, c1);
+    RingUse u{};
+    char *h = ring_reserve(st, bytes, u);
+    if (use)
+        *use = u;
+    return h;
 }
 
-void *qs_stage(qs_state *st, const void *host, size_t bytes)
+char *qs_ring_upload(qs_state *st, const char *h, size_t bytes, const RingUse &use)
 {
-    int c0, c1;
-    char *h = ring_reserve(st, bytes, c0, c1);
-    if (!h)
-        return nullptr;
     char *d = st->dring + (h - st->hring);
-    std::memcpy(h, host, bytes);
     hipError_t e = hipMemcpyAsync(d, h, bytes, hipMemcpyHostToDevice, st->stream);
     if (e != hipSuccess) {
         qs_hip_fail(e, "hipMemcpyAsync(staging ring)");
         return nullptr;
     }
-    for (int c = c0; c <= c1; ++c) {
+    for (int c = use.c0; c <= use.c1; ++c) {
         e = hipEventRecord(st->ring_ev[c], st->stream);
         if (e != hipSuccess) {
             qs_hip_fail(e, "hipEventRecord(staging ring)");
@@ -105,6 +103,16 @@ void *qs_stage(qs_state *st, const void *host, size_t bytes)
         st->ring_ev_live[c] = true;
     }
     return d;
+}
+
+void *qs_stage(qs_state *st, const void *host, size_t bytes)
+{
+    RingUse use;
+    char *h = ring_reserve(st, bytes, use);
+    if (!h)
+        return nullptr;
+    std::memcpy(h, host, bytes);
+    return qs_ring_upload(st, h, bytes, use);
 }
 
 char *qs_scratch(qs_state *st, size_t bytes)
@@ -261,6 +269,53 @@ void qs_permute_matrix(const double *U, int k, const int *perm, std::vector<doub
 }
 
 
+// Monomial matrix with every nonzero in {1, -1, i, -i} (exact) -> move table. Returns false otherwise.
+bool qs_monomial_table(const std::vector<double> &Us, int k, PermTable &pt)
+{
+    const int D = 1 << k;
+    std::memset(&pt, 0, sizeof pt);
+    std::vector<int> colseen(D, 0);
+    for (int a = 0; a < D; ++a) {
+        int found = -1, ph = 0;
+        for (int b = 0; b < D; ++b) {
+            const double re = Us[2 * (a * D + b)], im = Us[2 * (a * D + b) + 1];
+            if (re == 0.0 && im == 0.0)
+                continue;
+            if (found >= 0)
+                return false;
+            if (re == 1.0 && im == 0.0)
+                ph = 0;
+            else if (re == 0.0 && im == 1.0)
+                ph = 1;
+            else if (re == -1.0 && im == 0.0)
+                ph = 2;
+            else if (re == 0.0 && im == -1.0)
+                ph = 3;
+            else
+                return false;
+            found = b;
+        }
+        if (found < 0 || colseen[found])
+            return false;
+        colseen[found] = 1;
+        pt.src[a] = (uint8_t)found;
+        pt.phase[a] = (uint8_t)ph;
+        if (found != a || ph != 0)
+            pt.moving |= (uint64_t)1 << a;
+    }
+    return true;
+}
+
+bool qs_is_diagonal(const double *U, int k)
+{
+    const int D = 1 << k;
+    for (int a = 0; a < D; ++a)
+        for (int b = 0; b < D; ++b)
+            if (a != b && (U[2 * (a * D + b)] != 0.0 || U[2 * (a * D + b) + 1] != 0.0))
+                return false;
+    return true;
+}
+
 namespace {
 
 void release(qs_state *st)
@@ -303,53 +358,6 @@ int check_qubits(const qs_state *st, const int *q, int cnt, const char *what, ui
     }
     *mask = m;
     return QS_OK;
-}
-
-// Monomial matrix with every nonzero in {1, -1, i, -i} (exact) -> move table. Returns false otherwise.
-bool monomial_table(const std::vector<double> &Us, int k, PermTable &pt)
-{
-    const int D = 1 << k;
-    std::memset(&pt, 0, sizeof pt);
-    std::vector<int> colseen(D, 0);
-    for (int a = 0; a < D; ++a) {
-        int found = -1, ph = 0;
-        for (int b = 0; b < D; ++b) {
-            const double re = Us[2 * (a * D + b)], im = Us[2 * (a * D + b) + 1];
-            if (re == 0.0 && im == 0.0)
-                continue;
-            if (found >= 0)
-                return false;
-            if (re == 1.0 && im == 0.0)
-                ph = 0;
-            else if (re == 0.0 && im == 1.0)
-                ph = 1;
-            else if (re == -1.0 && im == 0.0)
-                ph = 2;
-            else if (re == 0.0 && im == -1.0)
-                ph = 3;
-            else
-                return false;
-            found = b;
-        }
-        if (found < 0 || colseen[found])
-            return false;
-        colseen[found] = 1;
-        pt.src[a] = (uint8_t)found;
-        pt.phase[a] = (uint8_t)ph;
-        if (found != a || ph != 0)
-            pt.moving |= (uint64_t)1 << a;
-    }
-    return true;
-}
-
-bool is_diagonal(const double *U, int k)
-{
-    const int D = 1 << k;
-    for (int a = 0; a < D; ++a)
-        for (int b = 0; b < D; ++b)
-            if (a != b && (U[2 * (a * D + b)] != 0.0 || U[2 * (a * D + b) + 1] != 0.0))
-                return false;
-    return true;
 }
 
 int diag_impl(qs_state *st, const int *targets, int k, const double *d);
@@ -439,7 +447,7 @@ int matrix_impl(qs_state *st, const int *targets, int k, uint64_t tmask, uint64_
     const int nins = __builtin_popcountll(tmask | cmask);
     const uint64_t ngroups = (uint64_t)1 << (n - nins);
     PermTable pt;
-    if (monomial_table(Us, k, pt)) {
+    if (qs_monomial_table(Us, k, pt)) {
         if (!pt.moving)
             return QS_OK;  // identity
         int rc = QS_OK;
@@ -687,7 +695,7 @@ QS_API int qs_apply_gate(qs_state *st, const int *targets, int k, const double *
     uint64_t tmask;
     if (int rc = check_qubits(st, targets, k, "targets", &tmask))
         return rc;
-    if (is_diagonal(U, k)) {
+    if (qs_is_diagonal(U, k)) {
         // exactly diagonal: entries on the diagonal, in the same bit order
         const int D = 1 << k;
         std::vector<double> d((size_t)2 * D);

@@ -67,9 +67,14 @@ double *qs_block_partials(qs_state *st, size_t n);
 // Copy `bytes` of host data to the device through the staging ring (async on st->stream). Returns the device
 // address, or nullptr on failure (error already recorded).
 void *qs_stage(qs_state *st, const void *host, size_t bytes);
-// `bytes` of the ring's pinned host memory that no copy still reads, for a caller that waits for its use of them before
-// it returns (nullptr and the error recorded on failure).
-char *qs_ring_host(qs_state *st, size_t bytes);
+// `bytes` of the ring's pinned host memory that no copy still reads (nullptr and the error recorded on failure). The
+// caller waits for its own use of them before it returns, or fills them and has qs_ring_upload copy them to the device
+// (async on st->stream; returns the device address, or nullptr and the error recorded).
+struct RingUse {
+    int c0, c1;  // ring chunks taken
+};
+char *qs_ring_host(qs_state *st, size_t bytes, RingUse *use = nullptr);
+char *qs_ring_upload(qs_state *st, const char *h, size_t bytes, const RingUse &use);
 // Device scratch of at least `bytes` that the state keeps until qs_scratch_drop or its end (nullptr and the error
 // recorded on failure); ordered by the state's stream.
 char *qs_scratch(qs_state *st, size_t bytes);
@@ -80,6 +85,11 @@ inline size_t amp_bytes(int dtype) { return dtype == QS_C128 ? 16 : 8; }
 // host helpers (qs_api.hip): ascending target order, matrix in ascending target order (qs_make_ins: qs_index.h)
 void qs_sort_targets(const int *t, int k, TPos &tp, int *perm);
 void qs_permute_matrix(const double *U, int k, const int *perm, std::vector<double> &out);
+
+bool qs_is_diagonal(const double *U, int k);
+struct PermTable;
+// Monomial matrix (sorted order) with every nonzero in {1, -1, i, -i} (exact) -> move table. Returns false otherwise.
+bool qs_monomial_table(const std::vector<double> &Us, int k, PermTable &pt);
 
 // ------------------------------------------------------------------------------------------------------------
 // kernel argument blocks (passed by value)
@@ -136,6 +146,23 @@ hipError_t launch_scale(int dtype, void *psi, uint64_t dim, double f, hipStream_
 hipError_t launch_scale_dev(int dtype, void *psi, uint64_t dim, const double *norm_dev, hipStream_t s);
 // *result = the sum of partials[0..nb) in a fixed order (FP64)
 hipError_t launch_sum_partials(const double *partials, int nb, double *result, hipStream_t s);
+
+// Circuits on states that fit one workgroup's LDS (qs_small.hip): the operations as a program for one launch, formed on
+// the host. Operations are added with valid arguments for the state they will run on.
+struct SmallProgram {
+    int dtype = QS_C128;
+    size_t nops = 0;           // operations of the circuit it was formed from
+    std::vector<char> chunks;  // whole chunks of records
+    size_t used = 0;           // bytes of the last chunk
+    size_t last_dense1 = SIZE_MAX;  // where in it the last record starts, if that is a 1-qubit gate
+    std::vector<char> pool;    // larger matrices and tables
+};
+// state bytes up to which a circuit runs that way (the largest power of two in a CU's 160 KiB of LDS)
+inline size_t qs_small_bytes() { return (size_t)128 << 10; }
+void qs_small_add_matrix(SmallProgram &P, const int *t, int k, const int *c, int nc, const double *U);
+void qs_small_add_diag(SmallProgram &P, const int *t, int k, const double *d);
+void qs_small_add_swap(SmallProgram &P, int p, int q, int s);
+int qs_small_run(qs_state *st, const SmallProgram &P);
 
 // LDS block passes: local qubit set L (ascending global positions), stage table in device memory
 constexpr int kMaxBlockOpK = 3;

@@ -18,6 +18,8 @@
 #include <cmath>
 #include <complex>
 #include <cstring>
+#include <memory>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -116,6 +118,10 @@ struct qs_circuit {
     int n = 0;
     std::vector<RawOp> raw;
     std::vector<PG> gates;
+    // the circuit as a program for small states, per precision (host memory only; formed again when operations were
+    // added since). Circuits are shared between threads that run them, so it is handed out under a lock.
+    mutable std::mutex small_mu;
+    mutable std::shared_ptr<const SmallProgram> small[2];
 };
 
 struct PlanPass {
@@ -450,6 +456,51 @@ int run_raw(qs_state *st, const RawOp &r)
     }
 }
 
+// Whether a plain run of circuit c on st goes as one launch over LDS (qs_small.hip): the state fits, and there are
+// operations enough that one launch and the copy of its program (13 us in a stream of runs, 21 us alone, up to 13 qubits
+// complex64 and 12 complex128; 17 and 28 us on 13 qubits complex128) beat a launch each (6 operations: 17-24 and 27-29
+// us; 4 operations: 11-13 and 22-24).
+// Not under stream capture: a replayed graph would read the program from the staging ring after it has been reused.
+constexpr size_t kSmallMinOps = 6;
+constexpr size_t kSmallProgramMax = (size_t)2 << 20;  // bytes; the staging ring has 8 MiB
+bool small_eligible(const qs_state *st, const qs_circuit *c)
+{
+    if (((size_t)1 << st->n) * amp_bytes(st->dtype) > qs_small_bytes() || c->raw.size() < kSmallMinOps)
+        return false;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st->stream, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return cs == hipStreamCaptureStatusNone;
+}
+
+// The circuit's program, or null if it is too long for the staging ring or does not fit host memory.
+std::shared_ptr<const SmallProgram> small_program(const qs_circuit *c, int dtype)
+try {
+    std::lock_guard<std::mutex> lock(c->small_mu);
+    std::shared_ptr<const SmallProgram> &have = c->small[dtype];
+    if (!have || have->nops != c->raw.size()) {
+        auto P = std::make_shared<SmallProgram>();
+        P->dtype = dtype;
+        for (const RawOp &r : c->raw) {
+            if (P->chunks.size() + P->pool.size() > kSmallProgramMax)
+                break;  // too long for the ring: what is there says so
+            if (r.kind == 3)
+                qs_small_add_swap(*P, r.p, r.q, r.s);
+            else if (r.kind == 1)
+                qs_small_add_diag(*P, r.t.data(), (int)r.t.size(), r.m.data());
+            else
+                qs_small_add_matrix(*P, r.t.data(), (int)r.t.size(), r.c.data(), (int)r.c.size(), r.m.data());
+        }
+        P->nops = c->raw.size();
+        have = std::move(P);
+    }
+    return have->chunks.size() + have->pool.size() <= kSmallProgramMax ? have : nullptr;
+} catch (const std::bad_alloc &) {
+    return nullptr;
+}
+
 // Each buffer is recorded in the plan as soon as it exists, so upload() can release whatever a failed attempt left.
 int upload_tables(qs_plan *P)
 {
@@ -675,6 +726,9 @@ QS_API int qs_circuit_run(qs_state *st, const qs_circuit *c)
         return qs_fail(QS_EINVAL, "qs_circuit_run: NULL argument");
     if (c->n != st->n)
         return qs_fail(QS_EINVAL, "qs_circuit_run: circuit has %d qubits, state has %d", c->n, st->n);
+    if (small_eligible(st, c))
+        if (const std::shared_ptr<const SmallProgram> P = small_program(c, st->dtype))
+            return qs_small_run(st, *P);
     for (const RawOp &r : c->raw)
         if (int rc = run_raw(st, r))
             return rc;
