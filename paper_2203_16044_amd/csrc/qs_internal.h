@@ -139,13 +139,15 @@ hipError_t launch_diag_sparse(int dtype, void *psi, uint64_t nsub, const InsBits
 
 hipError_t launch_fused_swap(int dtype, void *psi, int n, int lo, int hi, int s_, hipStream_t s);
 
+// out: 2^n probabilities, or null; result: their sum, or null (host: also written there, pinned host memory)
 hipError_t launch_probs(int dtype, const void *psi, uint64_t dim, double *out, double *partials, int nblocks,
-                        double *result, hipStream_t s);
+                        double *result, hipStream_t s, double *host = nullptr);
 int probs_blocks(uint64_t dim);
 hipError_t launch_scale(int dtype, void *psi, uint64_t dim, double f, hipStream_t s);
 hipError_t launch_scale_dev(int dtype, void *psi, uint64_t dim, const double *norm_dev, hipStream_t s);
 // *result = the sum of partials[0..nb) in a fixed order (FP64)
-hipError_t launch_sum_partials(const double *partials, int nb, double *result, hipStream_t s);
+// (host: also written there, pinned host memory)
+hipError_t launch_sum_partials(const double *partials, int nb, double *result, hipStream_t s, double *host = nullptr);
 
 // Circuits on states that fit one workgroup's LDS (qs_small.hip): the operations as a program for one launch, formed on
 // the host. Operations are added with valid arguments for the state they will run on.
