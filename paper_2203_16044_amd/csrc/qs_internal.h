@@ -117,6 +117,12 @@ hipError_t launch_perm_lanes(int dtype, void *psi, int n, const PermLanes &pl, h
 hipError_t launch_init_zero(int dtype, void *psi, uint64_t dim, hipStream_t s);
 hipError_t launch_dense(int dtype, int k, void *psi, uint64_t ngroups, const InsBits &ins, const TPos &tp,
                         const double *U_host_sorted, const void *U_dev, hipStream_t s);
+// Whether an uncontrolled 1-qubit gate on target t runs in the lane-exchange kernel (its pair partner lies in the same
+// wave: 6.3-6.6 TB/s on every such target where the group form reached 5.5-6.0, 32 qubits).
+inline bool qs_dense1_in_lanes(int dtype, int n, int t)
+{
+    return t < (dtype == QS_C128 ? 6 : 7) && n >= (dtype == QS_C128 ? 6 : 7);
+}
 hipError_t launch_dense_mfma(int dtype, int k, void *psi, uint64_t ngroups, const InsBits &ins, const TPos &tp,
                              const void *U_dev, hipStream_t s);
 hipError_t launch_perm(int dtype, int k, void *psi, uint64_t ngroups, const InsBits &ins, const TPos &tp,
@@ -152,7 +158,7 @@ hipError_t launch_sum_partials(const double *partials, int nb, double *result, h
 // Circuits on states that fit one workgroup's LDS (qs_small.hip): the operations as a program for one launch, formed on
 // the host. Operations are added with valid arguments for the state they will run on.
 struct SmallProgram {
-    int dtype = QS_C128;
+    int dtype = QS_C128, n = 0;
     size_t nops = 0;           // operations of the circuit it was formed from
     std::vector<char> chunks;  // whole chunks of records
     size_t used = 0;           // bytes of the last chunk

@@ -839,11 +839,10 @@ hipError_t dense_k(void *psi, uint64_t ngroups, const InsBits &ins, const TPos &
             m.v[i] = (R)Uh[i];
         if constexpr (K == 1) {
             // a plain 1-qubit gate (no controls) whose partner lies inside the wave: the lane-exchange form
-            // (measured faster than the group form on every such target: 6.3 vs 5.5-6.0 TB/s)
-            const int lane_limit = sizeof(R) == 8 ? 6 : 7;
             const uint64_t dim = ngroups * 2;
             const uint64_t nvec = sizeof(R) == 8 ? dim : dim / 2;
-            if (ins.np == 1 && ins.orm == 0 && tp.tpos[0] < lane_limit && nvec >= 64 && nvec % 64 == 0) {
+            if (ins.np == 1 && ins.orm == 0 &&
+                qs_dense1_in_lanes(sizeof(R) == 8 ? QS_C128 : QS_C64, __builtin_ctzll(dim), tp.tpos[0])) {
                 hipLaunchKernelGGL((k_dense1_lane<R>), dim3(grid_for(nvec, bs)), dim3(bs), 0, s,
                                    (typename LaneVec<R>::T *)psi, nvec, tp.tpos[0], m);
                 return hipGetLastError();

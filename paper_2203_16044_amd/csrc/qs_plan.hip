@@ -483,6 +483,7 @@ try {
     if (!have || have->nops != c->raw.size()) {
         auto P = std::make_shared<SmallProgram>();
         P->dtype = dtype;
+        P->n = c->n;
         for (const RawOp &r : c->raw) {
             if (P->chunks.size() + P->pool.size() > kSmallProgramMax)
                 break;  // too long for the ring: what is there says so

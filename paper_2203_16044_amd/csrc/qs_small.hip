@@ -11,8 +11,9 @@
 // pool behind them. The program is formed once per circuit and precision, on the host, and goes to the device through
 // the state's staging ring with each run.
 //
-// Arithmetic per operation is that of the one-pass kernels: matrix entries applied in FMA chains in ascending column
-// order; monomial gates with entries 1, -1, i, -i and fused-swaps are pure moves; diagonal entries 1 leave amplitudes
+// Arithmetic per operation is that of the one-pass kernels, rounding for rounding (1-qubit gates the lane-exchange form
+// takes there in its order, matrix entries otherwise in FMA chains in ascending column order, 5 and 6 targets complex64
+// in the order of the matrix-core tiles), so that complex64 results are the single calls' bit for bit; monomial gates with entries 1, -1, i, -i and fused-swaps are pure moves; diagonal entries 1 leave amplitudes
 // untouched, -1 flips signs.
 #include <algorithm>
 #include <cstring>
@@ -46,7 +47,8 @@ struct Rec {
     uint32_t k;          // targets
     uint64_t pos;        // target positions, 4 bits each; swap: lo, hi, s, 8 bits each
     uint32_t table;      // moves and diagonals on at most 2 targets: 4 bits per member (source and phase, or code); one
-                         // target: the second position repeats the first, so that members 0 and 3 are named
+                         // target: the second position repeats the first, so that members 0 and 3 are named; 1-qubit
+                         // gates: bits 0 and 1, the first and second gate in the lane-exchange order
     uint32_t off;        // byte offset of the matrix or table in the pool
 };
 static_assert(sizeof(Rec) == 32, "program record");
@@ -104,9 +106,19 @@ template <class C2, class R> __device__ __forceinline__ void mul_add(R &yr, R &y
     yi = fma(ui, x.x, yi);
 }
 
-template <class C2, class R> __device__ __forceinline__ void pair_gate(C2 &a, C2 &b, const R *u)
+// lane: in the order of the lane-exchange kernel (own member's products last), else column by column.
+template <class C2, class R> __device__ __forceinline__ void pair_gate(C2 &a, C2 &b, const R *u, bool lane)
 {
     C2 y{0, 0}, z{0, 0};
+    if (lane) {
+        y.x = fma(u[0], a.x, fma(-u[1], a.y, fma(u[2], b.x, -u[3] * b.y)));
+        y.y = fma(u[0], a.y, fma(u[1], a.x, fma(u[2], b.y, u[3] * b.x)));
+        z.x = fma(u[6], b.x, fma(-u[7], b.y, fma(u[4], a.x, -u[5] * a.y)));
+        z.y = fma(u[6], b.y, fma(u[7], b.x, fma(u[4], a.y, u[5] * a.x)));
+        a = y;
+        b = z;
+        return;
+    }
     mul_add(y.x, y.y, u[0], u[1], a);
     mul_add(y.x, y.y, u[2], u[3], b);
     mul_add(z.x, z.y, u[4], u[5], a);
@@ -217,15 +229,16 @@ __global__ __launch_bounds__(1024) void k_small(typename ST<R>::C2 *__restrict__
                         reals<16>(f.m, u);
                     const uint32_t lo = p0 < p1 ? p0 : p1, hi = p0 < p1 ? p1 : p0;
                     const uint32_t o0 = 1u << p0, o1 = 1u << p1;
+                    const bool l0 = table & 1u, l1 = table & 2u;
 #pragma unroll
                     for (int it = 0; it < Q4; ++it) {
                         const uint32_t g = tid + it * NT, i = insert0(insert0(g, lo), hi);
                         if (g < dim / 4) {
                             C2 a = s[i], b = s[i | o0], c = s[i | o1], d = s[i | o0 | o1];
-                            pair_gate(a, b, u);
-                            pair_gate(c, d, u);
-                            pair_gate(a, c, u + 8);
-                            pair_gate(b, d, u + 8);
+                            pair_gate(a, b, u, l0);
+                            pair_gate(c, d, u, l0);
+                            pair_gate(a, c, u + 8, l1);
+                            pair_gate(b, d, u + 8, l1);
                             s[i] = a;
                             s[i | o0] = b;
                             s[i | o1] = c;
@@ -238,7 +251,7 @@ __global__ __launch_bounds__(1024) void k_small(typename ST<R>::C2 *__restrict__
                         const uint32_t g = tid + it * NT, i = insert0(g, p0);
                         if (g < dim / 2 && (i & cmask) == cmask) {
                             C2 a = s[i], b = s[i | tmask];
-                            pair_gate(a, b, u);
+                            pair_gate(a, b, u, table & 1u);
                             s[i] = a;
                             s[i | tmask] = b;
                         }
@@ -361,10 +374,40 @@ __global__ __launch_bounds__(1024) void k_small(typename ST<R>::C2 *__restrict__
                             const R *row = U + ((size_t)a << (k + 1));
                             uint32_t sub = 0;  // the members' offsets, ascending
                             y = C2{0, 0};
+                            if (sizeof(R) == 4 && k >= 5) {
+                                // four members' real parts, then their imaginary parts; quads alternate between sums
+                                C2 odd{0, 0};
+                                for (uint32_t b = 0; b < (1u << k); b += 4) {
+                                    C2 x[4];
+#pragma unroll
+                                    for (int e = 0; e < 4; ++e) {
+                                        x[e] = s[base | sub];
+                                        sub = (sub - tmask) & tmask;
+                                    }
+                                    C2 acc = b & 4u ? odd : y;
+#pragma unroll
+                                    for (int e = 0; e < 4; ++e) {
+                                        acc.x = fma(row[2 * (b + e)], x[e].x, acc.x);
+                                        acc.y = fma(row[2 * (b + e) + 1], x[e].x, acc.y);
+                                    }
+#pragma unroll
+                                    for (int e = 0; e < 4; ++e) {
+                                        acc.x = fma(-row[2 * (b + e) + 1], x[e].y, acc.x);
+                                        acc.y = fma(row[2 * (b + e)], x[e].y, acc.y);
+                                    }
+                                    if (b & 4u)
+                                        odd = acc;
+                                    else
+                                        y = acc;
+                                }
+                                y.x += odd.x;
+                                y.y += odd.y;
+                            } else {
 #pragma unroll 4
-                            for (uint32_t b = 0; b < (1u << k); ++b) {
-                                mul_add(y.x, y.y, row[2 * b], row[2 * b + 1], s[base | sub]);
-                                sub = (sub - tmask) & tmask;
+                                for (uint32_t b = 0; b < (1u << k); ++b) {
+                                    mul_add(y.x, y.y, row[2 * b], row[2 * b + 1], s[base | sub]);
+                                    sub = (sub - tmask) & tmask;
+                                }
                             }
                         }
                     }
@@ -444,6 +487,7 @@ bool join_dense1(SmallProgram &P, const Rec &r, const double *U)
         return false;
     first.kind_size = OP_DENSE11 | (uint32_t)(2 + 2 * mat / 16) << 8;
     first.tmask |= r.tmask;
+    first.table |= r.table << 1;
     first.k = 2;
     first.pos |= r.pos << 4;
     std::memcpy(p, &first, sizeof first);
@@ -540,6 +584,8 @@ void qs_small_add_matrix(SmallProgram &P, const int *t, int k, const int *c, int
         return;
     }
     if (k <= 2) {
+        if (k == 1 && nc == 0)
+            r.table = qs_dense1_in_lanes(P.dtype, P.n, tp.tpos[0]) ? 1 : 0;
         if (k == 1 && nc == 0 && join_dense1(P, r, Us.data()))
             return;
         emit(P, r, k == 1 ? OP_DENSE1 : OP_DENSE2, Us.data(), Us.size());
