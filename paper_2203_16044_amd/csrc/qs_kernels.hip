@@ -52,20 +52,13 @@ template <class T> __device__ __forceinline__ void st(T *p, T v, int nt)
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// dense k-qubit gate, k <= 4: the group's 2^k members live in registers; U comes from kernel arguments
-// (k <= 3) or from device memory through uniform (scalar) loads (k = 4).
+// dense k-qubit gate, k <= 3: the group's 2^k members live in registers; U comes from kernel arguments.
 // ---------------------------------------------------------------------------------------------------------
 template <class R, int K> struct MatByVal {
     R v[2 << (2 * K)];
     __device__ __forceinline__ R re(int i) const { return v[2 * i]; }
     __device__ __forceinline__ R im(int i) const { return v[2 * i + 1]; }
 };
-template <class R> struct MatByPtr {
-    const R *__restrict__ p;
-    __device__ __forceinline__ R re(int i) const { return p[2 * i]; }
-    __device__ __forceinline__ R im(int i) const { return p[2 * i + 1]; }
-};
-
 // ---------------------------------------------------------------------------------------------------------
 // 1-qubit gate whose target lies inside a wave's contiguous span (complex128: q < 6; complex64: q < 7). Every lane
 // streams one 16-byte vector (one complex128 amplitude, or two adjacent complex64 ones) with full-width coalesced
@@ -858,10 +851,6 @@ hipError_t dense_k(void *psi, uint64_t ngroups, const InsBits &ins, const TPos &
             hipLaunchKernelGGL((k_dense<R, K, 1, MatByVal<R, K>>), dim3(grid_for(ngroups, bs)), dim3(bs), 0, s,
                                (C2 *)psi, ngroups, ins, tp, m, tu.nontemporal);
         }
-    } else if constexpr (K == 4) {
-        MatByPtr<R> m{(const R *)Ud};
-        hipLaunchKernelGGL((k_dense<R, 4, 1, MatByPtr<R>>), dim3(grid_for(ngroups, bs)), dim3(bs), 0, s, (C2 *)psi,
-                           ngroups, ins, tp, m, tu.nontemporal);
     } else {
         return launch_dense_mfma(std::is_same<R, double>::value ? QS_C128 : QS_C64, K, psi, ngroups, ins, tp, Ud, s);
     }
