@@ -220,9 +220,11 @@ struct BlkStageOp {  // host-side op table (planner statistics and batch relocat
 // Fused stage matrices of one pass (complex64): pool offsets (real elements) of n 16 x 16 complex matrices, row-major
 // and interleaved, whose stage index bit j <-> stage position pos[j]; the kernel keeps them in LDS.
 constexpr int kMaxMfmaStages = 4;
+constexpr uint32_t kWarmMax = 12288;  // bytes: of a 16 KiB scalar cache, beside the stage records
 struct BlkMfma {
     int n = 0;
     uint32_t off[kMaxMfmaStages] = {0, 0, 0, 0};
+    uint32_t warm_at = 0, warm = 0;  // the pass's op matrices: pool offset (real elements), bytes to fetch ahead
 };
 // A renormalisation folded into a complex64 block pass (both optional, device pointers): scale_norm, the state is
 // scaled by 1 / sqrt(*scale_norm) as each block is loaded; norm_part, one FP64 partial sum of |amplitude|^2 per

@@ -133,6 +133,7 @@ struct PlanPass {
     int stage_begin = 0, nstages = 0;  // block: range in stages
     int sw = 4;                        // block: register stage width (3 or 4)
     BlkMfma mf{};                      // block, complex64: fused stage matrices run on the matrix cores
+    uint32_t mat_begin = 0, mat_end = 0;  // block: the stages' matrices in the pool (real elements)
     // dense
     int k = 0;
     TPos tp{};
@@ -1112,6 +1113,7 @@ int append_pass(qs_plan *P, const qs_circuit *c, int mode, const std::vector<int
     std::vector<char> placed(nf, 0);
     int left = nf;
     pp.stage_begin = (int)P->stages.size();
+    pp.mat_begin = (uint32_t)P->pool.size();
     std::vector<std::vector<int>> stage_members;  // fused-op indices of each stage of this pass, in order
     while (left) {
         uint32_t S = 0;
@@ -1190,6 +1192,7 @@ int append_pass(qs_plan *P, const qs_circuit *c, int mode, const std::vector<int
         P->stages.push_back(stg);
     }
     pp.nstages = (int)P->stages.size() - pp.stage_begin;
+    pp.mat_end = (uint32_t)P->pool.size();
     for (const std::vector<int> &members : stage_members)
         for (int i : members)
             for (int gi : fused[i].members)
@@ -1492,8 +1495,11 @@ int run_pass(qs_state *st, qs_plan *P, int i, const BlkRenorm &rn)
     switch (pp.type) {
     case 0: {
         const InsBits outer = qs_make_ins(pp.lmask, 0);
+        BlkMfma mf = pp.mf;
+        mf.warm_at = pp.mat_begin;
+        mf.warm = std::min<uint32_t>((pp.mat_end - pp.mat_begin) * (uint32_t)esz, kWarmMax);
         QS_HIP(launch_block(st->dtype, pp.b, pp.sw, st->psi, (uint64_t)1 << (P->n - pp.b), outer, pp.bm,
-                            P->dstages + pp.stage_begin, pp.nstages, P->dpool, pp.mf,
+                            P->dstages + pp.stage_begin, pp.nstages, P->dpool, mf,
                             pp.lstage_begin >= 0 ? P->dlstages + pp.lstage_begin : nullptr, st->stream, rn));
         break;
     }
