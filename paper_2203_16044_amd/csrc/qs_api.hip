@@ -563,21 +563,22 @@ int diag_impl(qs_state *st, const int *targets, int k, const double *d)
     da.k = k;
     for (int j = 0; j < k; ++j)
         da.t[j] = targets[j];
-    const void *dd = nullptr, *cd = nullptr;
-    if (k > 2) {
+    const void *dd = nullptr;
+    if (k > 6) {  // beyond the kernel-argument budget: entries and classes through the staging ring
+        std::vector<char> tab(amp_bytes(st->dtype) * D + D);
         if (st->dtype == QS_C128) {
-            dd = qs_stage(st, d, (size_t)2 * D * sizeof(double));
+            std::memcpy(tab.data(), d, (size_t)2 * D * sizeof(double));
         } else {
-            std::vector<float> f(d, d + 2 * D);
-            dd = qs_stage(st, f.data(), f.size() * sizeof(float));
+            float *f = reinterpret_cast<float *>(tab.data());
+            for (int a = 0; a < 2 * D; ++a)
+                f[a] = (float)d[a];
         }
+        std::memcpy(tab.data() + amp_bytes(st->dtype) * D, cls.data(), cls.size());
+        dd = qs_stage(st, tab.data(), tab.size());
         if (!dd)
             return QS_EDEVICE;
-        cd = qs_stage(st, cls.data(), cls.size());
-        if (!cd)
-            return QS_EDEVICE;
     }
-    QS_HIP(launch_diag_full(st->dtype, st->psi, (uint64_t)1 << st->n, da, d, dd, cls.data(), cd, st->stream));
+    QS_HIP(launch_diag_full(st->dtype, st->psi, (uint64_t)1 << st->n, da, d, dd, cls.data(), st->stream));
     return QS_OK;
 }
 

@@ -7,6 +7,7 @@
 // member stream is a coalesced 16-byte-per-lane stream whenever its bit positions are not the lowest ones.
 #include "qs_internal.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace {
@@ -81,14 +82,14 @@ __device__ __forceinline__ void pair_out(R ar, R ai, R br, R bi, int bit, const 
     outi = fma(ur, ai, fma(ui, ar, fma(vr, bi, vi * br)));
 }
 
-template <class R>
+template <class R, bool NT>
 __global__ __launch_bounds__(256) void k_dense1_lane(typename LaneVec<R>::T *__restrict__ psi, uint64_t nvec, int q,
                                                      MatByVal<R, 1> m)
 {
     using V = typename LaneVec<R>::T;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; v < nvec; v += stride) {
-        const V x = __builtin_nontemporal_load(psi + v);
+        const V x = NT ? __builtin_nontemporal_load(psi + v) : psi[v];
         V y;
         if constexpr (sizeof(R) == 8) {
             const int d = 1 << q;
@@ -121,10 +122,12 @@ __global__ __launch_bounds__(256) void k_dense1_lane(typename LaneVec<R>::T *__r
                 y.w = o3;
             }
         }
-        __builtin_nontemporal_store(y, psi + v);
+        if constexpr (NT)
+            __builtin_nontemporal_store(y, psi + v);
+        else
+            psi[v] = y;
     }
 }
-
 
 template <class R, int K, int G, class MS>
 __global__ __launch_bounds__(256) void k_dense(typename CT<R>::T *__restrict__ psi, uint64_t ngroups, InsBits ins,
@@ -236,7 +239,7 @@ __global__ __launch_bounds__(256) void k_perm(typename CT<R>::T *__restrict__ ps
 // of the 2^H combinations of the out-of-wave qubits of Q, so every access is a whole line in lane order, and each
 // output takes its source from the lane, vector slot and member the move table names, by cross-lane reads. Which
 // source feeds an output depends only on the lane, so it is worked out once per thread.
-template <class R, int H>
+template <class R, int H, bool NT>
 __global__ __launch_bounds__(256) void k_perm_lanes(typename LaneVec<R>::T *__restrict__ psi, uint64_t nchunks,
                                                     InsBits ins_h, PermLanes pl)
 {
@@ -286,7 +289,7 @@ __global__ __launch_bounds__(256) void k_perm_lanes(typename LaneVec<R>::T *__re
         V v[M];
 #pragma unroll
         for (int m = 0; m < M; ++m)
-            v[m] = __builtin_nontemporal_load(psi + base + hoff[m] / P);
+            v[m] = NT ? __builtin_nontemporal_load(psi + base + hoff[m] / P) : psi[base + hoff[m] / P];
 #pragma unroll
         for (int m = 0; m < M; ++m) {
             V y;
@@ -317,7 +320,10 @@ __global__ __launch_bounds__(256) void k_perm_lanes(typename LaneVec<R>::T *__re
                 y[2 * p] = z.x;
                 y[2 * p + 1] = z.y;
             }
-            __builtin_nontemporal_store(y, psi + base + hoff[m] / P);
+            if constexpr (NT)
+                __builtin_nontemporal_store(y, psi + base + hoff[m] / P);
+            else
+                psi[base + hoff[m] / P] = y;
         }
     }
 }
@@ -325,124 +331,135 @@ __global__ __launch_bounds__(256) void k_perm_lanes(typename LaneVec<R>::T *__re
 // ---------------------------------------------------------------------------------------------------------
 // diagonal gates
 // ---------------------------------------------------------------------------------------------------------
-struct DiagSmall {  // k <= 2: entries and classes in kernel arguments (selected, never indexed)
-    double re[4], im[4];
-    int cls[4];  // 0: untouched (entry exactly 1), 1: negate (exactly -1), 2: multiply
+// Streaming diagonals, one 16-byte vector (one complex128 amplitude, two complex64 ones) per thread. cls: 4 bits per
+// entry, 0: untouched (entry exactly 1), 1: negate (exactly -1), 2: multiply.
+template <class R> struct DiagSmall {  // k <= 2: entries and classes in kernel arguments, selected, never indexed
+    R re[4], im[4];
+    uint32_t cls;
 };
 
-template <class R, int K, int G>
-__global__ __launch_bounds__(256) void k_diag_small(typename CT<R>::T *__restrict__ psi, uint64_t dim, DiagArgs da,
-                                                    DiagSmall ds)
+template <class R> __device__ __forceinline__ void diag_apply(R &x, R &y, uint32_t cls, R dr, R di)
 {
-    using C2 = typename CT<R>::T;
-    const uint64_t bs = blockDim.x;
-    const uint64_t stride = (uint64_t)gridDim.x * bs * G;
-    for (uint64_t i0 = (uint64_t)blockIdx.x * bs * G + threadIdx.x; i0 < dim; i0 += stride) {
-        C2 x[G];
-        int cl[G], pa[G];
-#pragma unroll
-        for (int j = 0; j < G; ++j) {
-            const uint64_t i = i0 + j * bs;
-            int a = 0;
-#pragma unroll
-            for (int q = 0; q < K; ++q)
-                a |= (int)((i >> da.t[q]) & 1) << q;
-            pa[j] = a;
-            cl[j] = i < dim ? ds.cls[a] : 0;
-            if (cl[j])
-                x[j] = ld(psi + i, 1);
-        }
-#pragma unroll
-        for (int j = 0; j < G; ++j) {
-            if (!cl[j])
-                continue;
-            const uint64_t i = i0 + j * bs;
-            C2 y;
-            if (cl[j] == 1) {
-                y.x = -x[j].x;
-                y.y = -x[j].y;
-            } else {
-                const R dr = (R)ds.re[pa[j]], di = (R)ds.im[pa[j]];
-                y.x = fma(dr, x[j].x, -di * x[j].y);
-                y.y = fma(dr, x[j].y, di * x[j].x);
-            }
-            st(psi + i, y, 1);
-        }
-    }
+    const R r = fma(dr, x, -di * y), i = fma(dr, y, di * x);
+    x = cls == 2 ? r : cls == 1 ? -x : x;
+    y = cls == 2 ? i : cls == 1 ? -y : y;
 }
 
-// complex64, k <= 2: each lane takes two adjacent amplitudes as one 16-byte vector (full-width lanes); a vector
-// whose two entries are both 1 is neither read nor written, otherwise both are rewritten (an entry of 1 leaves
-// its amplitude's bits unchanged).
-template <int K>
-__global__ __launch_bounds__(256) void k_diag_small_f2(float4 *__restrict__ psi, uint64_t nvec, DiagArgs da,
-                                                       DiagSmall ds)
+// Bound by HBM. The entries come from scalar registers by selection: indexed by the lane they were loads of their own,
+// in front of the amplitude's. 27 qubits, RZ: complex128 659 us against 740, complex64 328 against
+// 411; 23 qubits 37 against 47 and 20 against 27.
+template <class R, int K, bool NT>
+__global__ __launch_bounds__(256) void k_diag_small(typename LaneVec<R>::T *__restrict__ psi, uint64_t nvec,
+                                                    int t0, int t1, DiagSmall<R> ds)
 {
-    typedef float F4 __attribute__((ext_vector_type(4)));
+    using V = typename LaneVec<R>::T;
+    constexpr int P = sizeof(R) == 8 ? 1 : 2;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; v < nvec; v += stride) {
-        int cl[2], pa[2];
+        uint32_t cl[P];
+        bool b0[P], b1[P];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const uint64_t i = 2 * v + h;
-            int a = 0;
-#pragma unroll
-            for (int q = 0; q < K; ++q)
-                a |= (int)((i >> da.t[q]) & 1) << q;
-            pa[h] = a;
-            cl[h] = ds.cls[a];
+        for (int h = 0; h < P; ++h) {
+            const uint64_t i = v * P + h;
+            b0[h] = (i >> t0) & 1;
+            b1[h] = K == 2 && ((i >> t1) & 1);
+            cl[h] = (ds.cls >> (4 * ((int)b0[h] + 2 * (int)b1[h]))) & 15u;
         }
-        if (!cl[0] && !cl[1])
+        if (!(cl[0] | cl[P - 1]))
             continue;
-        F4 x = __builtin_nontemporal_load(reinterpret_cast<const F4 *>(psi + v));
-        float re[2] = {x.x, x.z}, im[2] = {x.y, x.w};
+        V x = NT ? __builtin_nontemporal_load(psi + v) : psi[v];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            if (cl[h] == 1) {
-                re[h] = -re[h];
-                im[h] = -im[h];
-            } else if (cl[h] == 2) {
-                const float dr = (float)ds.re[pa[h]], di = (float)ds.im[pa[h]];
-                const float r = fmaf(dr, re[h], -di * im[h]);
-                im[h] = fmaf(dr, im[h], di * re[h]);
-                re[h] = r;
+        for (int h = 0; h < P; ++h) {
+            R dr = b0[h] ? ds.re[1] : ds.re[0], di = b0[h] ? ds.im[1] : ds.im[0];
+            if constexpr (K == 2) {
+                dr = b1[h] ? (b0[h] ? ds.re[3] : ds.re[2]) : dr;
+                di = b1[h] ? (b0[h] ? ds.im[3] : ds.im[2]) : di;
             }
+            R re = x[2 * h], im = x[2 * h + 1];
+            diag_apply(re, im, cl[h], dr, di);
+            x[2 * h] = re;
+            x[2 * h + 1] = im;
         }
-        F4 y;
-        y.x = re[0];
-        y.y = im[0];
-        y.z = re[1];
-        y.w = im[1];
-        __builtin_nontemporal_store(y, reinterpret_cast<F4 *>(psi + v));
+        if constexpr (NT)
+            __builtin_nontemporal_store(x, psi + v);
+        else
+            psi[v] = x;
     }
 }
 
-// k >= 3: the 2^k entries (in the compute precision) and classes come from device memory.
-template <class R>
-__global__ __launch_bounds__(256) void k_diag_table(typename CT<R>::T *__restrict__ psi, uint64_t dim, DiagArgs da,
-                                                    const R *__restrict__ d, const uint8_t *__restrict__ cls)
+// k >= 3: the 2^k entries (in the compute precision) and classes come from a table: for k <= 6 in the kernel's own
+// arguments (through the staging ring two copies a gate made a 3-qubit diagonal on 21 qubits take 29 us; 9 us now),
+// beyond in device memory. The index bits above a block's vectors are the block's: they are gathered on the scalar unit.
+// 27 qubits, 3 targets: complex128 676 us against 746, complex64 369 against 606. full: no entry is 1, and the loads need
+// not wait for their class; otherwise an amplitude whose entry is 1 is not accessed.
+template <class R> struct DiagTable {
+    R d[128];
+    uint8_t cls[64];
+};
+template <class R, bool NT>
+__device__ __forceinline__ void diag_stream(typename LaneVec<R>::T *__restrict__ psi, uint64_t nvec, const DiagArgs &da,
+                                            const R *d, const uint8_t *cls, int full)
 {
-    using C2 = typename CT<R>::T;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < dim;
-         i += (uint64_t)gridDim.x * blockDim.x) {
-        int a = 0;
-        for (int q = 0; q < da.k; ++q)
-            a |= (int)((i >> da.t[q]) & 1) << q;
-        const int c = cls[a];
-        if (!c)
-            continue;
-        const C2 x = psi[i];
-        C2 y;
-        if (c == 1) {
-            y.x = -x.x;
-            y.y = -x.y;
-        } else {
-            const R dr = d[2 * a], di = d[2 * a + 1];
-            y.x = fma(dr, x.x, -di * x.y);
-            y.y = fma(dr, x.y, di * x.x);
+    using V = typename LaneVec<R>::T;
+    constexpr int P = sizeof(R) == 8 ? 1 : 2;
+    constexpr int LB = P == 1 ? 8 : 9;  // index bits within a block's vectors
+    const uint32_t low = threadIdx.x * P;
+    for (uint64_t b = blockIdx.x; b * 256 < nvec; b += gridDim.x) {
+        const uint64_t v = b * 256 + threadIdx.x;
+        if (v >= nvec)
+            return;
+        V x;
+        if (full)
+            x = NT ? __builtin_nontemporal_load(psi + v) : psi[v];
+        uint32_t ab = 0, a0 = 0, a1 = 0;
+        for (int q = 0; q < da.k; ++q) {
+            const int t = da.t[q];
+            if (t >= LB) {
+                ab |= (uint32_t)((b * 256 * P >> t) & 1) << q;
+            } else {
+                a0 |= ((low >> t) & 1u) << q;
+                a1 |= (((low | 1u) >> t) & 1u) << q;
+            }
         }
-        psi[i] = y;
+        const uint32_t a[2] = {ab | a0, ab | a1};
+        if (full) {
+#pragma unroll
+            for (int h = 0; h < P; ++h) {
+                R re = x[2 * h], im = x[2 * h + 1];
+                diag_apply(re, im, cls[a[h]], d[2 * a[h]], d[2 * a[h] + 1]);
+                x[2 * h] = re;
+                x[2 * h + 1] = im;
+            }
+            if constexpr (NT)
+                __builtin_nontemporal_store(x, psi + v);
+            else
+                psi[v] = x;
+            continue;
+        }
+        typename CT<R>::T *amp = reinterpret_cast<typename CT<R>::T *>(psi + v);
+#pragma unroll
+        for (int h = 0; h < P; ++h) {
+            const uint32_t c = cls[a[h]];
+            if (!c)
+                continue;
+            typename CT<R>::T z = ld(amp + h, NT);
+            diag_apply(z.x, z.y, c, d[2 * a[h]], d[2 * a[h] + 1]);
+            st(amp + h, z, NT);
+        }
     }
+}
+template <class R, bool NT>
+__global__ __launch_bounds__(256) void k_diag_args(typename LaneVec<R>::T *__restrict__ psi, uint64_t nvec, DiagArgs da,
+                                                   DiagTable<R> tab, int full)
+{
+    diag_stream<R, NT>(psi, nvec, da, tab.d, tab.cls, full);
+}
+template <class R, bool NT>
+__global__ __launch_bounds__(256) void k_diag_table(typename LaneVec<R>::T *__restrict__ psi, uint64_t nvec, DiagArgs da,
+                                                    const R *__restrict__ d, const uint8_t *__restrict__ cls,
+                                                    int full)
+{
+    diag_stream<R, NT>(psi, nvec, da, d, cls, full);
 }
 
 struct SparseArgs {
@@ -451,7 +468,7 @@ struct SparseArgs {
 };
 
 // Only the subspaces whose pattern has an entry != 1 are visited: blockIdx.y selects the pattern.
-template <class R, int G>
+template <class R, int G, bool NT>
 __global__ __launch_bounds__(256) void k_diag_sparse(typename CT<R>::T *__restrict__ psi, uint64_t nsub,
                                                      InsBits ins, SparseArgs sa)
 {
@@ -467,7 +484,7 @@ __global__ __launch_bounds__(256) void k_diag_sparse(typename CT<R>::T *__restri
             const uint64_t g = g0 + j * bs;
             idx[j] = ins0(g < nsub ? g : 0, ins) | e.orm;
             if (g < nsub)
-                x[j] = ld(psi + idx[j], 1);
+                x[j] = ld(psi + idx[j], NT);
         }
 #pragma unroll
         for (int j = 0; j < G; ++j) {
@@ -482,7 +499,7 @@ __global__ __launch_bounds__(256) void k_diag_sparse(typename CT<R>::T *__restri
                 y.x = fma(dr, x[j].x, -di * x[j].y);
                 y.y = fma(dr, x[j].y, di * x[j].x);
             }
-            st(psi + idx[j], y, 1);
+            st(psi + idx[j], y, NT);
         }
     }
 }
@@ -704,17 +721,24 @@ __global__ __launch_bounds__(256) void k_sum_partials(const double *__restrict__
     }
 }
 
-template <class R>
-__global__ __launch_bounds__(256) void k_scale(typename CT<R>::T *__restrict__ psi, uint64_t dim, double f,
+// One 16-byte vector per thread, factor and products in FP64. 27 qubits: complex128 653 us against 797, complex64 330
+// against 352 with one amplitude per thread and step.
+template <class R, bool NT>
+__global__ __launch_bounds__(256) void k_scale(typename LaneVec<R>::T *__restrict__ psi, uint64_t nvec, double f,
                                                const double *__restrict__ norm_dev)
 {
+    using V = typename LaneVec<R>::T;
     const double ff = norm_dev ? 1.0 / sqrt(*norm_dev) : f;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < dim;
-         i += (uint64_t)gridDim.x * blockDim.x) {
-        auto x = psi[i];
-        x.x = (R)((double)x.x * ff);
-        x.y = (R)((double)x.y * ff);
-        psi[i] = x;
+    for (uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; v < nvec;
+         v += (uint64_t)gridDim.x * blockDim.x) {
+        V x = NT ? __builtin_nontemporal_load(psi + v) : psi[v];
+#pragma unroll
+        for (int e = 0; e < (int)(16 / sizeof(R)); ++e)
+            x[e] = (R)((double)x[e] * ff);
+        if constexpr (NT)
+            __builtin_nontemporal_store(x, psi + v);
+        else
+            psi[v] = x;
     }
 }
 
@@ -806,11 +830,13 @@ hipError_t launch_init_zero(int dtype, void *psi, uint64_t dim, hipStream_t s)
 }
 
 namespace {
-// Non-temporal accesses help streams of whole cache lines; when a target sits inside a 128-byte line the
+// Non-temporal accesses help streams of whole cache lines from HBM; when a target sits inside a 128-byte line the
 // members of a group share lines across load instructions, so the loads go through the cache instead.
-template <class R> int nt_for(const TPos &tp, int k)
+template <class R> int nt_for(const TPos &tp, int k, uint64_t ngroups, const InsBits &ins)
 {
     const int line_bits = sizeof(typename CT<R>::T) == 16 ? 3 : 4;
+    if (!qs_streams((ngroups << ins.np) * sizeof(typename CT<R>::T)))
+        return 0;
     for (int j = 0; j < k; ++j)
         if (tp.tpos[j] < line_bits)
             return 0;
@@ -824,7 +850,7 @@ hipError_t dense_k(void *psi, uint64_t ngroups, const InsBits &ins, const TPos &
     using C2 = typename CT<R>::T;
     struct {
         int dense_gpt, nontemporal;
-    } tu{qs_tunables().dense_gpt.load(), nt_for<R>(tp, K)};
+    } tu{qs_tunables().dense_gpt.load(), nt_for<R>(tp, K, ngroups, ins)};
     const int bs = 256;
     if constexpr (K <= 3) {
         MatByVal<R, K> m;
@@ -836,8 +862,13 @@ hipError_t dense_k(void *psi, uint64_t ngroups, const InsBits &ins, const TPos &
             const uint64_t nvec = sizeof(R) == 8 ? dim : dim / 2;
             if (ins.np == 1 && ins.orm == 0 &&
                 qs_dense1_in_lanes(sizeof(R) == 8 ? QS_C128 : QS_C64, __builtin_ctzll(dim), tp.tpos[0])) {
-                hipLaunchKernelGGL((k_dense1_lane<R>), dim3(grid_for(nvec, bs)), dim3(bs), 0, s,
-                                   (typename LaneVec<R>::T *)psi, nvec, tp.tpos[0], m);
+                using V = typename LaneVec<R>::T;
+                if (qs_streams(nvec * 16))
+                    hipLaunchKernelGGL((k_dense1_lane<R, true>), dim3(grid_for(nvec, bs)), dim3(bs), 0, s, (V *)psi,
+                                       nvec, tp.tpos[0], m);
+                else
+                    hipLaunchKernelGGL((k_dense1_lane<R, false>), dim3(grid_for(nvec, bs)), dim3(bs), 0, s, (V *)psi,
+                                       nvec, tp.tpos[0], m);
                 return hipGetLastError();
             }
         }
@@ -878,7 +909,7 @@ hipError_t perm_k(void *psi, uint64_t ngroups, const InsBits &ins, const TPos &t
     using C2 = typename CT<R>::T;
     constexpr int G = 1;
     hipLaunchKernelGGL((k_perm<R, K, G>), dim3(grid_for(ngroups, 256 * G)), dim3(256), 0, s, (C2 *)psi, ngroups, ins,
-                       tp, pt, nt_for<R>(tp, K));
+                       tp, pt, nt_for<R>(tp, K, ngroups, ins));
     return hipGetLastError();
 }
 
@@ -927,61 +958,80 @@ hipError_t launch_perm_lanes(int dtype, void *psi, int n, const PermLanes &pl, h
     const InsBits ins_h = qs_make_ins(hmask, 0);
     const uint64_t nchunks = (uint64_t)1 << (n - LB - h);
     const unsigned g = grid_for(nchunks * 64, 256);
+    const bool nt = qs_streams(((uint64_t)1 << n) * amp_bytes(dtype));
+    auto go = [&](auto kernel, auto *p) {
+        hipLaunchKernelGGL(kernel, dim3(g), dim3(256), 0, s, p, nchunks, ins_h, pl);
+        return hipGetLastError();
+    };
     if (dtype == QS_C128) {
-        using V = LaneVec<double>::T;
-        if (h == 0)
-            hipLaunchKernelGGL((k_perm_lanes<double, 0>), dim3(g), dim3(256), 0, s, (V *)psi, nchunks, ins_h, pl);
-        else if (h == 1)
-            hipLaunchKernelGGL((k_perm_lanes<double, 1>), dim3(g), dim3(256), 0, s, (V *)psi, nchunks, ins_h, pl);
+        auto *p = (LaneVec<double>::T *)psi;
+        switch (2 * h + nt) {
+        case 0: return go(k_perm_lanes<double, 0, false>, p);
+        case 1: return go(k_perm_lanes<double, 0, true>, p);
+        case 2: return go(k_perm_lanes<double, 1, false>, p);
+        case 3: return go(k_perm_lanes<double, 1, true>, p);
+        case 4: return go(k_perm_lanes<double, 2, false>, p);
+        default: return go(k_perm_lanes<double, 2, true>, p);
+        }
+    }
+    auto *p = (LaneVec<float>::T *)psi;
+    switch (2 * h + nt) {
+    case 0: return go(k_perm_lanes<float, 0, false>, p);
+    case 1: return go(k_perm_lanes<float, 0, true>, p);
+    case 2: return go(k_perm_lanes<float, 1, false>, p);
+    case 3: return go(k_perm_lanes<float, 1, true>, p);
+    case 4: return go(k_perm_lanes<float, 2, false>, p);
+    default: return go(k_perm_lanes<float, 2, true>, p);
+    }
+}
+
+namespace {
+template <class R, bool NT>
+hipError_t diag_r(void *psi_, uint64_t dim, const DiagArgs &da, const double *d, const void *d_dev, const uint8_t *cls,
+                  hipStream_t s)
+{
+    using V = typename LaneVec<R>::T;
+    V *psi = (V *)psi_;
+    const uint64_t nvec = sizeof(R) == 8 ? dim : dim / 2;
+    const dim3 g(grid_for(nvec, 256)), b(256);
+    const int D = 1 << da.k;
+    const int full = std::find(cls, cls + D, 0) == cls + D;
+    if (da.k <= 2) {
+        DiagSmall<R> ds{};
+        for (int a = 0; a < D; ++a) {
+            ds.re[a] = (R)d[2 * a];
+            ds.im[a] = (R)d[2 * a + 1];
+            ds.cls |= (uint32_t)cls[a] << (4 * a);
+        }
+        if (da.k == 1)
+            hipLaunchKernelGGL((k_diag_small<R, 1, NT>), g, b, 0, s, psi, nvec, da.t[0], 0, ds);
         else
-            hipLaunchKernelGGL((k_perm_lanes<double, 2>), dim3(g), dim3(256), 0, s, (V *)psi, nchunks, ins_h, pl);
+            hipLaunchKernelGGL((k_diag_small<R, 2, NT>), g, b, 0, s, psi, nvec, da.t[0], da.t[1], ds);
+    } else if (da.k <= 6) {
+        DiagTable<R> tab;
+        for (int a = 0; a < 2 * D; ++a)
+            tab.d[a] = (R)d[a];
+        for (int a = 0; a < D; ++a)
+            tab.cls[a] = cls[a];
+        hipLaunchKernelGGL((k_diag_args<R, NT>), g, b, 0, s, psi, nvec, da, tab, full);
     } else {
-        using V = LaneVec<float>::T;
-        if (h == 0)
-            hipLaunchKernelGGL((k_perm_lanes<float, 0>), dim3(g), dim3(256), 0, s, (V *)psi, nchunks, ins_h, pl);
-        else if (h == 1)
-            hipLaunchKernelGGL((k_perm_lanes<float, 1>), dim3(g), dim3(256), 0, s, (V *)psi, nchunks, ins_h, pl);
-        else
-            hipLaunchKernelGGL((k_perm_lanes<float, 2>), dim3(g), dim3(256), 0, s, (V *)psi, nchunks, ins_h, pl);
+        const R *dd = (const R *)d_dev;
+        hipLaunchKernelGGL((k_diag_table<R, NT>), g, b, 0, s, psi, nvec, da, dd, (const uint8_t *)(dd + 2 * D),
+                           full);
     }
     return hipGetLastError();
 }
+}  // namespace
 
-hipError_t launch_diag_full(int dtype, void *psi, uint64_t dim, const DiagArgs &da, const double *d_host,
-                            const void *d_dev, const uint8_t *cls_host, const void *cls_dev, hipStream_t s)
+hipError_t launch_diag_full(int dtype, void *psi, uint64_t dim, const DiagArgs &da, const double *d, const void *d_dev,
+                            const uint8_t *cls, hipStream_t s)
 {
-    const int G = 1;
-    if (da.k <= 2) {
-        DiagSmall ds{};
-        for (int a = 0; a < (1 << da.k); ++a) {
-            ds.re[a] = d_host[2 * a];
-            ds.im[a] = d_host[2 * a + 1];
-            ds.cls[a] = cls_host[a];
-        }
-        const unsigned g = grid_for(dim, 256 * G);
-        if (dtype == QS_C128) {
-            if (da.k == 1)
-                hipLaunchKernelGGL((k_diag_small<double, 1, G>), dim3(g), dim3(256), 0, s, (double2 *)psi, dim, da, ds);
-            else
-                hipLaunchKernelGGL((k_diag_small<double, 2, G>), dim3(g), dim3(256), 0, s, (double2 *)psi, dim, da, ds);
-        } else {
-            const uint64_t nvec = dim / 2;
-            const unsigned gv = grid_for(nvec, 256);
-            if (da.k == 1)
-                hipLaunchKernelGGL((k_diag_small_f2<1>), dim3(gv), dim3(256), 0, s, (float4 *)psi, nvec, da, ds);
-            else
-                hipLaunchKernelGGL((k_diag_small_f2<2>), dim3(gv), dim3(256), 0, s, (float4 *)psi, nvec, da, ds);
-        }
-    } else {
-        const unsigned g = grid_for(dim, 256);
-        if (dtype == QS_C128)
-            hipLaunchKernelGGL(k_diag_table<double>, dim3(g), dim3(256), 0, s, (double2 *)psi, dim, da,
-                               (const double *)d_dev, (const uint8_t *)cls_dev);
-        else
-            hipLaunchKernelGGL(k_diag_table<float>, dim3(g), dim3(256), 0, s, (float2 *)psi, dim, da,
-                               (const float *)d_dev, (const uint8_t *)cls_dev);
-    }
-    return hipGetLastError();
+    const bool nt = qs_streams(dim * amp_bytes(dtype));
+    if (dtype == QS_C128)
+        return nt ? diag_r<double, true>(psi, dim, da, d, d_dev, cls, s)
+                  : diag_r<double, false>(psi, dim, da, d, d_dev, cls, s);
+    return nt ? diag_r<float, true>(psi, dim, da, d, d_dev, cls, s)
+              : diag_r<float, false>(psi, dim, da, d, d_dev, cls, s);
 }
 
 hipError_t launch_diag_sparse(int dtype, void *psi, uint64_t nsub, const InsBits &ins, int m,
@@ -994,11 +1044,19 @@ hipError_t launch_diag_sparse(int dtype, void *psi, uint64_t nsub, const InsBits
     for (int i = 0; i < m; ++i)
         sa.e[i] = ent[i];
     const int G = 1;
-    const dim3 grid(grid_for(nsub, 256 * G), m);
-    if (dtype == QS_C128)
-        hipLaunchKernelGGL((k_diag_sparse<double, G>), grid, dim3(256), 0, s, (double2 *)psi, nsub, ins, sa);
-    else
-        hipLaunchKernelGGL((k_diag_sparse<float, G>), grid, dim3(256), 0, s, (float2 *)psi, nsub, ins, sa);
+    const dim3 grid(grid_for(nsub, 256 * G), m), b(256);
+    const bool nt = qs_streams((nsub << ins.np) * amp_bytes(dtype));
+    if (dtype == QS_C128) {
+        if (nt)
+            hipLaunchKernelGGL((k_diag_sparse<double, G, true>), grid, b, 0, s, (double2 *)psi, nsub, ins, sa);
+        else
+            hipLaunchKernelGGL((k_diag_sparse<double, G, false>), grid, b, 0, s, (double2 *)psi, nsub, ins, sa);
+    } else {
+        if (nt)
+            hipLaunchKernelGGL((k_diag_sparse<float, G, true>), grid, b, 0, s, (float2 *)psi, nsub, ins, sa);
+        else
+            hipLaunchKernelGGL((k_diag_sparse<float, G, false>), grid, b, 0, s, (float2 *)psi, nsub, ins, sa);
+    }
     return hipGetLastError();
 }
 
@@ -1081,24 +1139,28 @@ hipError_t launch_sum_partials(const double *partials, int nb, double *result, h
     return hipGetLastError();
 }
 
+namespace {
+template <class R> hipError_t scale_r(void *psi, uint64_t dim, double f, const double *norm_dev, hipStream_t s)
+{
+    using V = typename LaneVec<R>::T;
+    const uint64_t nvec = sizeof(R) == 8 ? dim : dim / 2;
+    const dim3 g(grid_for(nvec, 256)), b(256);
+    if (qs_streams(nvec * 16))
+        hipLaunchKernelGGL((k_scale<R, true>), g, b, 0, s, (V *)psi, nvec, f, norm_dev);
+    else
+        hipLaunchKernelGGL((k_scale<R, false>), g, b, 0, s, (V *)psi, nvec, f, norm_dev);
+    return hipGetLastError();
+}
+}  // namespace
+
 hipError_t launch_scale(int dtype, void *psi, uint64_t dim, double f, hipStream_t s)
 {
-    const unsigned g = grid_for(dim, 256 * 4);
-    if (dtype == QS_C128)
-        hipLaunchKernelGGL(k_scale<double>, dim3(g), dim3(256), 0, s, (double2 *)psi, dim, f, (const double *)nullptr);
-    else
-        hipLaunchKernelGGL(k_scale<float>, dim3(g), dim3(256), 0, s, (float2 *)psi, dim, f, (const double *)nullptr);
-    return hipGetLastError();
+    return dtype == QS_C128 ? scale_r<double>(psi, dim, f, nullptr, s) : scale_r<float>(psi, dim, f, nullptr, s);
 }
 
 hipError_t launch_scale_dev(int dtype, void *psi, uint64_t dim, const double *norm_dev, hipStream_t s)
 {
-    const unsigned g = grid_for(dim, 256 * 4);
-    if (dtype == QS_C128)
-        hipLaunchKernelGGL(k_scale<double>, dim3(g), dim3(256), 0, s, (double2 *)psi, dim, 0.0, norm_dev);
-    else
-        hipLaunchKernelGGL(k_scale<float>, dim3(g), dim3(256), 0, s, (float2 *)psi, dim, 0.0, norm_dev);
-    return hipGetLastError();
+    return dtype == QS_C128 ? scale_r<double>(psi, dim, 0.0, norm_dev, s) : scale_r<float>(psi, dim, 0.0, norm_dev, s);
 }
 
 hipError_t launch_probe_copy(void *dst, const void *src, size_t bytes, hipStream_t s)

@@ -286,9 +286,6 @@ __global__ __launch_bounds__(256) void k_dense_mfma(typename MF<R>::C2 *__restri
     }
 }
 
-// Whether the amplitudes a gate touches exceed the 256 MiB last-level cache.
-bool big_state(uint64_t ngroups, int k, size_t amp) { return (ngroups << k) * amp >= ((uint64_t)256 << 20); }
-
 template <class R, int K, int CT, bool PAIR>
 hipError_t mfma_p(void *psi, uint64_t ngroups, const InsBits &ins, const TileMap &tm, const void *U, bool nt,
                   hipStream_t s)
@@ -344,7 +341,7 @@ hipError_t mfma_k(void *psi, uint64_t ngroups, const InsBits &ins, const TPos &t
     }
     // non-temporal where whole lines stream from HBM (27 qubits, k = 5 complex128: 682 us against 700, complex64 344
     // against 359), not on states the caches hold (22 qubits, k = 4 complex128: 28 us against 24)
-    const bool nt = !low_control && big_state(ngroups, K, sizeof(typename MF<R>::C2)) && qs_tunables().nontemporal;
+    const bool nt = !low_control && qs_streams((ngroups << K) * sizeof(typename MF<R>::C2)) && qs_tunables().nontemporal;
     if constexpr (sizeof(R) == 4)
         if (!(taken & ~tmask & 1))
             return mfma_p<R, K, CT, true>(psi, ngroups, ins, tm, U, nt, s);
