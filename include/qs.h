@@ -214,12 +214,16 @@ QS_API int qs_circuit_add_controlled(qs_circuit *c, const int *controls, int nc,
 QS_API int qs_circuit_add_fused_swap(qs_circuit *c, int p, int q, int s);
 /* Number of operations recorded. */
 QS_API int qs_circuit_size(const qs_circuit *c, int *nops);
-/* Plain execution: the qs_apply_* / qs_fused_swap calls of the circuit, in order (one pass each). Where the state is
- * at most 128 KiB, circuits of 6 operations and more run in one launch that keeps the state in a compute unit's LDS and
- * takes a pass over it per operation (two 1-qubit gates in a row on different qubits share one): pure moves, unit and
- * -1 diagonal entries stay exact, other results equal the single calls' up to rounding. Under stream capture each
- * operation is a launch of its own.
- * QS_EINVAL if the circuit's qubit count differs from the state's. */
+/* Plain execution: the qs_apply_* / qs_fused_swap calls of the circuit, in order, nothing fused or reordered. Pure moves
+ * and unit and -1 diagonal entries stay exact. Unless the stream is being captured (then each operation is a launch of
+ * its own), operations share passes over the state:
+ *   - Where the state is at most 64 KiB, circuits of 6 operations and more run in one launch that keeps the state in a
+ *     compute unit's LDS; results equal the single calls' up to rounding.
+ *   - Larger states (from one tile on, 64 KiB) take operations in a row on the qubits of one tile in one pass: gates
+ *     and controlled gates on 1 or 2 targets and diagonals on up to 6, bit for bit the single calls' results. Others,
+ *     and runs that would cost less as calls, are single calls.
+ * The passes' records go through the state's staging buffer with each run; formed once per circuit and precision, on the
+ * host. QS_EINVAL if the circuit's qubit count differs from the state's. */
 QS_API int qs_circuit_run(qs_state *st, const qs_circuit *c);
 
 enum {

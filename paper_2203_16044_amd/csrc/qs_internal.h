@@ -172,12 +172,49 @@ struct SmallProgram {
     size_t last_dense1 = SIZE_MAX;  // where in it the last record starts, if that is a 1-qubit gate
     std::vector<char> pool;    // larger matrices and tables
 };
-// state bytes up to which a circuit runs that way (the largest power of two in a CU's 160 KiB of LDS)
-inline size_t qs_small_bytes() { return (size_t)128 << 10; }
+// State bytes up to which a circuit runs that way (128 KiB would fit a CU's LDS; there the passes over tiles are faster:
+// layers of RZ, RX and CNOT on 13 qubits complex128, 252 operations, 383 us against 125 on 14).
+inline size_t qs_small_bytes() { return (size_t)64 << 10; }
 void qs_small_add_matrix(SmallProgram &P, const int *t, int k, const int *c, int nc, const double *U);
 void qs_small_add_diag(SmallProgram &P, const int *t, int k, const double *d);
 void qs_small_add_swap(SmallProgram &P, int p, int q, int s);
 int qs_small_run(qs_state *st, const SmallProgram &P);
+
+// Circuits on larger states (qs_tile.hip): operations in a row on the qubits of one tile as one pass over the state, the
+// others as calls. Formed on the host; raw: the operation's place in the circuit.
+struct TileOp {  // an operation of the pass being formed
+    int raw = 0, k = 0, nt = 0;  // nt: qubits it mixes or exchanges, ascending in t
+    int t[2] = {0, 0};
+    int d[6] = {0, 0, 0, 0, 0, 0};  // a diagonal's qubits, in the order of its entries' bits
+    uint64_t cmask = 0;
+    uint32_t kind = 0, table = 0, flags = 0;
+    double share = 1.0;  // of the state's 128-byte lines, that a call of its own reads and rewrites
+    std::vector<double> m;
+    std::vector<uint8_t> code;
+};
+struct TileStep {
+    int raw;          // an operation run as a call, or -1: a pass
+    uint64_t qubits;  // of the tile
+    size_t at, bytes; // its records
+    size_t staged;    // a call: bytes it takes of the staging ring
+};
+struct TileProgram {
+    int dtype = QS_C128, n = 0;
+    size_t nops = 0;   // operations of the circuit it was formed from
+    size_t calls = 0;  // steps that are calls
+    std::vector<char> prog;
+    std::vector<TileStep> steps;
+    std::vector<TileOp> open;
+    uint64_t open_qubits = 0;
+    size_t open_bytes = 0;
+};
+bool qs_tile_fits(int n, int dtype);
+void qs_tile_add_matrix(TileProgram &P, int raw, const int *t, int k, const int *c, int nc, const double *U);
+void qs_tile_add_diag(TileProgram &P, int raw, const int *t, int k, const double *d);
+void qs_tile_add_call(TileProgram &P, int raw, size_t staged);
+void qs_tile_finish(TileProgram &P);
+int qs_tile_upload(qs_state *st, const TileProgram &P, size_t i, size_t *end, const char **dev);
+int qs_tile_pass(qs_state *st, const TileStep &step, const char *dev);
 
 // LDS block passes: local qubit set L (ascending global positions), stage table in device memory
 constexpr int kMaxBlockOpK = 3;

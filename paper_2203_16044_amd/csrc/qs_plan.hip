@@ -122,6 +122,7 @@ struct qs_circuit {
     // added since). Circuits are shared between threads that run them, so it is handed out under a lock.
     mutable std::mutex small_mu;
     mutable std::shared_ptr<const SmallProgram> small[2];
+    mutable std::shared_ptr<const TileProgram> tile[2];  // the same for larger states
 };
 
 struct PlanPass {
@@ -457,23 +458,65 @@ int run_raw(qs_state *st, const RawOp &r)
     }
 }
 
-// Whether a plain run of circuit c on st goes as one launch over LDS (qs_small.hip): the state fits, and there are
-// operations enough that one launch and the copy of its program (13 us in a stream of runs, 21 us alone, up to 13 qubits
-// complex64 and 12 complex128; 17 and 28 us on 13 qubits complex128) beat a launch each (6 operations: 17-24 and 27-29
-// us; 4 operations: 11-13 and 22-24).
+// Whether a plain run of circuit c on st can go as one launch over LDS (qs_small.hip): the state fits, and there are
+// operations enough that one launch and the copy of its program (13 us in a stream of runs, 21 us alone) beat a launch
+// each (6 operations: 17-24 and 27-29 us; 4 operations: 11-13 and 22-24).
 // Not under stream capture: a replayed graph would read the program from the staging ring after it has been reused.
 constexpr size_t kSmallMinOps = 6;
 constexpr size_t kSmallProgramMax = (size_t)2 << 20;  // bytes; the staging ring has 8 MiB
 bool small_eligible(const qs_state *st, const qs_circuit *c)
 {
-    if (((size_t)1 << st->n) * amp_bytes(st->dtype) > qs_small_bytes() || c->raw.size() < kSmallMinOps)
-        return false;
+    return ((size_t)1 << st->n) * amp_bytes(st->dtype) <= qs_small_bytes() && c->raw.size() >= kSmallMinOps;
+}
+bool not_capturing(const qs_state *st)
+{
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st->stream, &cs) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
     return cs == hipStreamCaptureStatusNone;
+}
+
+// Operations in a row as passes over tiles (qs_tile.hip), or null if the program does not fit host memory.
+std::shared_ptr<const TileProgram> tile_program(const qs_circuit *c, int dtype)
+try {
+    std::lock_guard<std::mutex> lock(c->small_mu);
+    std::shared_ptr<const TileProgram> &have = c->tile[dtype];
+    if (!have || have->nops != c->raw.size()) {
+        auto P = std::make_shared<TileProgram>();
+        P->dtype = dtype;
+        P->n = c->n;
+        for (size_t i = 0; i < c->raw.size(); ++i) {
+            const RawOp &r = c->raw[i];
+            if (r.kind == 3)
+                qs_tile_add_call(*P, (int)i, 0);
+            else if (r.kind == 1)
+                qs_tile_add_diag(*P, (int)i, r.t.data(), (int)r.t.size(), r.m.data());
+            else
+                qs_tile_add_matrix(*P, (int)i, r.t.data(), (int)r.t.size(), r.c.data(), (int)r.c.size(), r.m.data());
+        }
+        qs_tile_finish(*P);
+        P->nops = c->raw.size();
+        have = std::move(P);
+    }
+    return have;
+} catch (const std::bad_alloc &) {
+    return nullptr;
+}
+
+int tile_run(qs_state *st, const qs_circuit *c, const TileProgram &P)
+{
+    const char *dev = nullptr;
+    for (size_t i = 0, end = 0; i < P.steps.size(); ++i) {
+        if (i == end)
+            if (int rc = qs_tile_upload(st, P, i, &end, &dev))
+                return rc;
+        const TileStep &s = P.steps[i];
+        if (int rc = s.raw < 0 ? qs_tile_pass(st, s, dev) : run_raw(st, c->raw[s.raw]))
+            return rc;
+    }
+    return QS_OK;
 }
 
 // The circuit's program, or null if it is too long for the staging ring or does not fit host memory.
@@ -728,9 +771,19 @@ QS_API int qs_circuit_run(qs_state *st, const qs_circuit *c)
         return qs_fail(QS_EINVAL, "qs_circuit_run: NULL argument");
     if (c->n != st->n)
         return qs_fail(QS_EINVAL, "qs_circuit_run: circuit has %d qubits, state has %d", c->n, st->n);
-    if (small_eligible(st, c))
-        if (const std::shared_ptr<const SmallProgram> P = small_program(c, st->dtype))
-            return qs_small_run(st, *P);
+    if (c->raw.size() > 1 && not_capturing(st)) {
+        // One tile exactly (64 KiB) is one workgroup's work either way, but passes hold the amplitudes in registers (12
+        // qubits complex128, 252 operations 89 us against 176), while calls in between (wide gates, fused-swaps) are
+        // launches that LDS saves (48 random operations, half of them calls, 310 us against 234) unless they are
+        // complex64, whose 8,192 amplitudes make a wide gate dearer on one compute unit than its launch (400 against 430).
+        if (qs_tile_fits(st->n, st->dtype))
+            if (const std::shared_ptr<const TileProgram> P = tile_program(c, st->dtype))
+                if (!small_eligible(st, c) || st->dtype == QS_C64 || 8 * P->calls <= c->raw.size())
+                    return tile_run(st, c, *P);
+        if (small_eligible(st, c))
+            if (const std::shared_ptr<const SmallProgram> P = small_program(c, st->dtype))
+                return qs_small_run(st, *P);
+    }
     for (const RawOp &r : c->raw)
         if (int rc = run_raw(st, r))
             return rc;

@@ -4,7 +4,7 @@
 // kernel computes for a fraction). Here one workgroup loads the state into LDS, applies the operations one after
 // another, each a pass over LDS with a workgroup barrier behind it, and writes the state back: 195 operations on 10
 // qubits (complex128) take 45 us against about 620 as 195 launches. What bounds an operation is the instructions a
-// wave issues for it (0.2 to 0.3 us up to 10 qubits), from 12 qubits on the LDS traffic (13 qubits complex128: 1.2 us).
+// wave issues for it (0.2 to 0.3 us up to 10 qubits), at 12 the LDS traffic as well.
 //
 // The circuit travels as a program: records of 32 bytes, those of 1- and 2-qubit gates followed by their matrix, packed
 // into 8 KiB chunks that the kernel brings into the scalar cache one at a time; larger matrices and tables lie in a
@@ -628,7 +628,6 @@ template <class R> hipError_t launch_r(qs_state *st, const char *prog, uint32_t 
     case 2: return launch_per<R, 2>(st, dim, nt, prog, bytes, pool);
     case 4: return launch_per<R, 4>(st, dim, nt, prog, bytes, pool);
     case 8: return launch_per<R, 8>(st, dim, nt, prog, bytes, pool);
-    case 16: return launch_per<R, 16>(st, dim, nt, prog, bytes, pool);
     default: return hipErrorInvalidValue;
     }
 }
