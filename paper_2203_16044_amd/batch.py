@@ -174,7 +174,7 @@ def autotune(circuits, dtype: str = "c128", cache: Optional[str] = CACHE, space:
 
 
 def plain_loop(circuits, dtype: str = "c128", keep: Iterable[int] = ()) -> Tuple[float, Dict[int, np.ndarray]]:
-    """The per-circuit plain loop: for each circuit allocate a state, apply its gates one pass each (qs_circuit_run)
+    """The per-circuit plain loop: for each circuit allocate a state, apply its gates in order (qs_circuit_run)
     and compute its FP64 probabilities. Returns (seconds on the stream, probabilities of the circuits in `keep`)."""
     import torch
 
