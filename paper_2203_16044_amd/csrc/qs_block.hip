@@ -655,6 +655,223 @@ __global__ __launch_bounds__(NT, (BlockBounds<R, B, W, NT>::waves_per_eu)) void 
 // exchange of the lane bit with a register bit it does not use (BlkStageL.swaps, chosen by the planner).
 // ---------------------------------------------------------------------------------------------------------
 
+// ------------------------------------------------------------------------------------------------------------
+// Complex128 stages in registers, one component at a time through LDS
+// ------------------------------------------------------------------------------------------------------------
+// A workgroup of 2^(B-4) threads holds a block in registers, 16 amplitudes a thread, and passes it through LDS between
+// stages, the real parts before the imaginary ones: half the LDS and no second copy in registers, so four workgroups of
+// 12-qubit blocks share a CU, and one's loads, LDS traffic and arithmetic go on beside the others'. Bound by FP64
+// arithmetic (76 % of the cycles) and HBM together: 12 2-qubit gates on 27 qubits 1032 us, two workgroups a CU with the
+// next block's loads in registers 1184; SU(4) layers on 31 qubits 273 ms against 290.
+
+// LDS slot (8 bytes) of local index m: swz, which sets apart the lowest four lane bits, and as the fifth bank bit the
+// parity of the bits in odd groups of four (linear over xor).
+__device__ __forceinline__ uint32_t slot8(uint32_t m)
+{
+    return swz(m) ^ (((m >> 5) ^ (m >> 6) ^ (m >> 7) ^ (m >> 12)) & 1u) << 4;
+}
+
+// The addend of a final product lives on past it, so that the product is a three-operand instruction into the register
+// of the amplitude it replaces (accumulated over the addend, results would be moved back).
+__device__ __forceinline__ void outlive(const double &t) { asm volatile("" ::"v"(t)); }
+// A value that the compiler neither computes ahead nor shares between cases.
+__device__ __forceinline__ void pin(double2 &z) { asm volatile("" : "+v"(z.x), "+v"(z.y)); }
+
+// N reals at p, uniform, into scalar registers, here and not earlier: all of a matrix at once would not fit them.
+template <int N> __device__ __forceinline__ void row_to(double (&m)[N], const double *p)
+{
+    asm volatile("" : "+s"(p));
+    const __attribute__((address_space(4))) double *c = (const __attribute__((address_space(4))) double *)p;
+#pragma unroll
+    for (int e = 0; e < N; ++e)
+        m[e] = c[e];
+}
+
+// reg_op of a 4-position stage, group by group and row by row, each result over its amplitude; sums in reg_op_to's order.
+template <int MASK> __device__ __forceinline__ void reg_op_over(double2 (&x)[16], const double *__restrict__ U)
+{
+    constexpr int K = __builtin_popcount(MASK), D = 1 << K;
+    constexpr int P0 = __builtin_ctz(MASK), M1 = MASK & (MASK - 1), P1 = M1 ? __builtin_ctz(M1) : 0;
+    constexpr int M2 = M1 & (M1 - 1), P2 = M2 ? __builtin_ctz(M2) : 0;
+    auto at = [](int a) { return (a & 1) << P0 | ((a >> 1) & 1) << P1 | ((a >> 2) & 1) << P2; };
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        if (r & MASK)
+            continue;
+        double2 y[D];
+        double last[D], m[2][2 * D];
+        row_to(m[0], U);
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+            if (a + 1 < D)
+                row_to(m[(a + 1) & 1], U + 2 * D * (a + 1));
+            const double *u = m[a & 1];
+            double yr = 0, yi = 0;
+#pragma unroll
+            for (int b = 0; b < D; ++b) {
+                const double2 v = x[r | at(b)];
+                yr = fma(u[2 * b], v.x, yr);
+                if (b < D - 1)
+                    yr = fma(-u[2 * b + 1], v.y, yr);
+                yi = fma(u[2 * b], v.y, yi);
+                if (b < D - 1)
+                    yi = fma(u[2 * b + 1], v.x, yi);
+            }
+            asm volatile("s_mov_b64 %0, %1" : "=s"(last[a]) : "s"(u[2 * D - 1]));  // registers of its own: it keeps no row
+            y[a].x = yr;
+            y[a].y = yi;
+            if (K > 1)
+                __builtin_amdgcn_sched_barrier(0);  // two rows in scalar registers
+        }
+        const double2 v = x[r | at(D - 1)];
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+            double2 z;
+            z.x = fma(-last[a], v.y, y[a].x);
+            z.y = fma(last[a], v.x, y[a].y);
+            outlive(y[a].x);
+            outlive(y[a].y);
+            x[r | at(a)] = z;
+        }
+#pragma unroll
+        for (int a = 0; a < D; ++a)
+            pin(x[r | at(a)]);
+    }
+}
+__device__ __forceinline__ void reg_op_over_dispatch(double2 (&x)[16], int mask, const double *__restrict__ U)
+{
+    switch (mask) {
+    case 1: reg_op_over<1>(x, U); break;
+    case 2: reg_op_over<2>(x, U); break;
+    case 3: reg_op_over<3>(x, U); break;
+    case 4: reg_op_over<4>(x, U); break;
+    case 5: reg_op_over<5>(x, U); break;
+    case 6: reg_op_over<6>(x, U); break;
+    case 7: reg_op_over<7>(x, U); break;
+    case 8: reg_op_over<8>(x, U); break;
+    case 9: reg_op_over<9>(x, U); break;
+    case 10: reg_op_over<10>(x, U); break;
+    case 11: reg_op_over<11>(x, U); break;
+    case 12: reg_op_over<12>(x, U); break;
+    case 13: reg_op_over<13>(x, U); break;
+    default: reg_op_over<14>(x, U); break;
+    }
+}
+
+// A stage's layout for a thread: the slot of its first member, and the stage positions' slots.
+struct Layout {
+    uint32_t s0, so[4];
+    __device__ __forceinline__ uint32_t operator()(int r) const
+    {
+        return s0 ^ (r & 1 ? so[0] : 0u) ^ (r & 2 ? so[1] : 0u) ^ (r & 4 ? so[2] : 0u) ^ (r & 8 ? so[3] : 0u);
+    }
+};
+template <int B> __device__ __forceinline__ Layout layout_of(const BlkStage &stg)
+{
+    Layout l;
+    uint32_t m = 0;
+#pragma unroll
+    for (int j = 0; j < B - 4; ++j)
+        m |= ((threadIdx.x >> j) & 1u) << stg.order[j];
+    l.s0 = slot8(m);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        l.so[j] = slot8(1u << stg.pos[j]);
+    return l;
+}
+// Load and store phase: member `it` is local index threadIdx.x + it 2^(B-4).
+template <int B> __device__ __forceinline__ Layout layout_lines()
+{
+    Layout l;
+    l.s0 = slot8(threadIdx.x);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        l.so[j] = slot8(1u << (B - 4 + j));
+    return l;
+}
+// From one layout to another. The slots of the first were the thread's own (or nobody's).
+__device__ __forceinline__ void through_lds(double *s, double2 (&x)[16], const Layout &from, const Layout &to)
+{
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+        s[from(r)] = x[r].x;
+    lds_barrier();
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+        x[r].x = s[to(r)];
+    lds_barrier();
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+        s[from(r)] = x[r].y;
+    lds_barrier();
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+        x[r].y = s[to(r)];
+}
+template <int B>
+__device__ __forceinline__ Layout run_stages(double *s, double2 (&x)[16], Layout at, const BlkStage *__restrict__ stages,
+                                             int nstages, const double *__restrict__ mats)
+{
+    for (int t = 0; t < nstages; ++t) {
+        const BlkStage &stg = stages[t];
+        const Layout to = layout_of<B>(stg);
+        through_lds(s, x, at, to);
+        at = to;
+        uint32_t moff = stg.mat_base;
+        const uint32_t masks = stg.masks;
+        const int nops = stg.nops;
+        for (int o = 0; o < nops; ++o) {
+            const int mask = (int)(masks >> (4 * o)) & 15;
+            reg_op_over_dispatch(x, mask, mats + moff);
+            moff += 2u << (2 * __builtin_popcount(mask));
+        }
+    }
+    return at;
+}
+
+template <int B, bool NT>
+__global__ __launch_bounds__(1 << (B - 4), 4) void k_block_c128(double2 *__restrict__ psi, InsBits outer, BlockMap bm,
+                                                                const BlkStage *__restrict__ stages, int nstages,
+                                                                const double *__restrict__ mats, uint32_t warm_at,
+                                                                uint32_t warm)
+{
+    using NV = NT2<double>::type;
+    constexpr int T = 1 << (B - 4);
+
+    extern __shared__ __align__(16) unsigned char smem_blk[];
+    double *s = reinterpret_cast<double *>(smem_blk);
+    NV *const pb = reinterpret_cast<NV *>(psi + (ins0b(NT ? xcd_runs(blockIdx.x, gridDim.x) : blockIdx.x, outer) |
+                                               spread(threadIdx.x, bm)));
+    uint64_t h[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        h[j] = (uint64_t)1 << bm.lpos[B - 4 + j];
+    double2 x[16];
+#pragma unroll
+    for (int it = 0; it < 16; ++it) {
+        const NV *a = pb + blk_hi<4>(h, it);
+        const NV v = NT ? __builtin_nontemporal_load(a) : *a;
+        x[it].x = v.x;
+        x[it].y = v.y;
+    }
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    warm_scalar(stages, nstages * (uint32_t)sizeof(BlkStage), wave, T >= 64 ? T / 64 : 1);
+    warm_scalar(mats + warm_at, warm, wave, T >= 64 ? T / 64 : 1);
+    const Layout at = run_stages<B>(s, x, layout_lines<B>(), stages, nstages, mats);
+    through_lds(s, x, at, layout_lines<B>());
+#pragma unroll
+    for (int it = 0; it < 16; ++it) {
+        NV *a = pb + blk_hi<4>(h, it);
+        NV v;
+        v.x = x[it].x;
+        v.y = x[it].y;
+        if constexpr (NT)
+            __builtin_nontemporal_store(v, a);
+        else
+            *a = v;
+    }
+}
+
 // Exchange of the lane bit (thread bit 5) with register bit RB: for every a with bit RB clear, the upper
 // half-wave's x[a] and the lower half-wave's x[a | 2^RB] trade places, which is what v_permlane32_swap does to
 // its two operands (upper 32 lanes of the first with the lower 32 lanes of the second), one 32-bit word at a time.
@@ -1293,6 +1510,22 @@ hipError_t block_b(void *psi, uint64_t nblocks, const InsBits &outer, const Bloc
     // persistent workgroups (each walks several blocks so its loads can run ahead of its arithmetic)
     const uint64_t cus = (uint64_t)qs_cu_count();
     const uint64_t grid = block_grid_nt(NT, nblocks);
+    // four blocks a CU and more: the kernel that keeps four there. Fewer are a question of latency, and one barrier a
+    // stage takes less of it than three (12-qubit blocks, microseconds a pass of SU(4) layers: 19 qubits 20.4 against
+    // 25.2, 21 qubits 26.7 against 31.5, 22 qubits 50.5 against 49.8, 24 qubits 180 against 174).
+    if constexpr (B >= 10 && W == 4 && sizeof(R) == 8) {
+        if (nblocks >= 4 * (uint64_t)qs_cu_count() && !lstages && !qs_tunables().block_async) {
+            const bool nt = qs_streams((nblocks << B) * 16);
+            auto go = [&](auto kernel) {
+                if (hipError_t e = qs_allow_lds((const void *)kernel, (size_t)8 << B))
+                    return e;
+                hipLaunchKernelGGL(kernel, dim3((unsigned)nblocks), dim3(1 << (B - 4)), (size_t)8 << B, s, (double2 *)psi,
+                                   outer, bm, stages, nstages, (const double *)mats, mf.warm_at, mf.warm);
+                return hipGetLastError();
+            };
+            return nt ? go(k_block_c128<B, true>) : go(k_block_c128<B, false>);
+        }
+    }
     if constexpr (B == 12 && W == 4 && sizeof(R) == 8) {
         if (lstages) {
             if (hipError_t e = qs_allow_lds((const void *)k_block_lanes, data))

@@ -319,6 +319,15 @@ hipError_t launch_batch_level(int dtype, int b, void *psi, double *probs, const 
 hipError_t launch_probe_copy(void *dst, const void *src, size_t bytes, hipStream_t s);
 hipError_t launch_probe_rmw(void *buf, size_t bytes, hipStream_t s);
 
+// The block that workgroup `b` of n (a power of two) takes. Workgroups go to the 8 XCDs in turn; neighbouring blocks
+// share DRAM pages when their qubits leave low index bits to the block number, and this way an XCD takes runs of 32 of
+// them (27 qubits complex128, a pass over qubits 0 to 2 and 9 to 17: 908 us, so 747; over seven sets of qubits 6 % on
+// average, runs of 8 the same, of 2 or of 128 less). For states in HBM; those in cache lose by it.
+__device__ __forceinline__ uint32_t xcd_runs(uint32_t b, uint64_t n)
+{
+    return n < 256 ? b : (b & ~255u) | (b & 7u) << 5 | ((b >> 3) & 31u);
+}
+
 // Workgroup barrier ordering LDS only: waits for this wave's LDS accesses (lgkmcnt) but not for its global loads
 // and stores, so prefetched loads and outstanding stores stay in flight across it (__syncthreads() would drain
 // them). Use only where the barrier protects LDS data.

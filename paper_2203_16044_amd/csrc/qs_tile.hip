@@ -14,7 +14,7 @@
 // A pass is bound by HBM up to about 16 1-qubit gates (complex128, 26 qubits: 0.40 ms with 4, 0.43 with 16, 0.55 with
 // 32; complex64, 27 qubits: 0.36, 0.54 and 0.98) and by the multiply-adds beyond: 4 waves a SIMD from different tiles
 // keep loads and arithmetic going at once. On small states an operation costs its instructions and the branches to them
-// (14 qubits: 0.4 us each). Circuits of U3, CZ, RZ and Toffoli layers, 3 layers: 28 qubits complex128 20.9 ms against
+// (14 qubits: 0.4 us each). Circuits of U3, CZ, RZ and Toffoli layers, 3 layers: 28 qubits complex128 20.3 ms against
 // 268 gate by gate, complex64 12.5 against 142; 20 qubits 177 us against 888; 14 qubits 86 us against 448.
 //
 // Operations with more than two targets to mix, and fused-swaps, stay calls of their own, as do runs whose operations
@@ -386,7 +386,7 @@ __global__ __launch_bounds__(1 << (TT<R>::B - kW)) void k_tile(typename TT<R>::C
     constexpr uint32_t T = 1u << (TT<R>::B - kW);
     extern __shared__ __align__(16) unsigned char smem[];
     const uint32_t tid = threadIdx.x;
-    const uint64_t base = qs_ins0(blockIdx.x, outer);
+    const uint64_t base = qs_ins0(NT ? xcd_runs(blockIdx.x, gridDim.x) : blockIdx.x, outer);
     C2 *const p = psi + base;
     cwords w = (cwords)prog;
     C2 x[kM];
