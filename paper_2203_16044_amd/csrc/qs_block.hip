@@ -688,24 +688,31 @@ template <int N> __device__ __forceinline__ void row_to(double (&m)[N], const do
 }
 
 // reg_op of a 4-position stage, group by group and row by row, each result over its amplitude; sums in reg_op_to's order.
-template <int MASK> __device__ __forceinline__ void reg_op_over(double2 (&x)[16], const double *__restrict__ U)
+template <int MASK>
+__device__ __forceinline__ void reg_op_over(double2 (&x)[16], const double *__restrict__ U, const double *next)
 {
     constexpr int K = __builtin_popcount(MASK), D = 1 << K;
     constexpr int P0 = __builtin_ctz(MASK), M1 = MASK & (MASK - 1), P1 = M1 ? __builtin_ctz(M1) : 0;
     constexpr int M2 = M1 & (M1 - 1), P2 = M2 ? __builtin_ctz(M2) : 0;
     auto at = [](int a) { return (a & 1) << P0 | ((a >> 1) & 1) << P1 | ((a >> 2) & 1) << P2; };
+    double all[K < 3 ? 2 * D * D : 1];
+    uint32_t t[4] = {};
+    if constexpr (K < 3)
+        row_to(all, U);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         if (r & MASK)
             continue;
         double2 y[D];
-        double last[D], m[2][2 * D];
-        row_to(m[0], U);
+        double last[D], m[2][K < 3 ? 1 : 2 * D];
+        if constexpr (K == 3)
+            row_to(m[0], U);
 #pragma unroll
         for (int a = 0; a < D; ++a) {
-            if (a + 1 < D)
-                row_to(m[(a + 1) & 1], U + 2 * D * (a + 1));
-            const double *u = m[a & 1];
+            if constexpr (K == 3)
+                if (a + 1 < D)
+                    row_to(m[(a + 1) & 1], U + 2 * D * (a + 1));
+            const double *u = K < 3 ? all + 2 * D * a : m[a & 1];
             double yr = 0, yi = 0;
 #pragma unroll
             for (int b = 0; b < D; ++b) {
@@ -717,10 +724,13 @@ template <int MASK> __device__ __forceinline__ void reg_op_over(double2 (&x)[16]
                 if (b < D - 1)
                     yi = fma(u[2 * b + 1], v.x, yi);
             }
-            asm volatile("s_mov_b64 %0, %1" : "=s"(last[a]) : "s"(u[2 * D - 1]));  // registers of its own: it keeps no row
+            if constexpr (K == 3)  // registers of its own: it keeps no row
+                asm volatile("s_mov_b64 %0, %1" : "=s"(last[a]) : "s"(u[2 * D - 1]));
+            else
+                last[a] = u[2 * D - 1];
             y[a].x = yr;
             y[a].y = yi;
-            if (K > 1)
+            if (K == 3)
                 __builtin_amdgcn_sched_barrier(0);  // two rows in scalar registers
         }
         const double2 v = x[r | at(D - 1)];
@@ -736,25 +746,37 @@ template <int MASK> __device__ __forceinline__ void reg_op_over(double2 (&x)[16]
 #pragma unroll
         for (int a = 0; a < D; ++a)
             pin(x[r | at(a)]);
+        if (K == 2 && r == 0) {  // the matrix is here: fetch the next one's lines
+            __builtin_amdgcn_sched_barrier(0);
+            typedef const __attribute__((address_space(4))) uint32_t *cwords;
+            cwords w = (cwords)next;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                t[e] = w[16 * e];
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
+    if (K == 2)
+        asm volatile("" ::"s"(t[0]), "s"(t[1]), "s"(t[2]), "s"(t[3]));
 }
-__device__ __forceinline__ void reg_op_over_dispatch(double2 (&x)[16], int mask, const double *__restrict__ U)
+__device__ __forceinline__ void reg_op_over_dispatch(double2 (&x)[16], int mask, const double *__restrict__ U,
+                                                     const double *next)
 {
     switch (mask) {
-    case 1: reg_op_over<1>(x, U); break;
-    case 2: reg_op_over<2>(x, U); break;
-    case 3: reg_op_over<3>(x, U); break;
-    case 4: reg_op_over<4>(x, U); break;
-    case 5: reg_op_over<5>(x, U); break;
-    case 6: reg_op_over<6>(x, U); break;
-    case 7: reg_op_over<7>(x, U); break;
-    case 8: reg_op_over<8>(x, U); break;
-    case 9: reg_op_over<9>(x, U); break;
-    case 10: reg_op_over<10>(x, U); break;
-    case 11: reg_op_over<11>(x, U); break;
-    case 12: reg_op_over<12>(x, U); break;
-    case 13: reg_op_over<13>(x, U); break;
-    default: reg_op_over<14>(x, U); break;
+    case 1: reg_op_over<1>(x, U, next); break;
+    case 2: reg_op_over<2>(x, U, next); break;
+    case 3: reg_op_over<3>(x, U, next); break;
+    case 4: reg_op_over<4>(x, U, next); break;
+    case 5: reg_op_over<5>(x, U, next); break;
+    case 6: reg_op_over<6>(x, U, next); break;
+    case 7: reg_op_over<7>(x, U, next); break;
+    case 8: reg_op_over<8>(x, U, next); break;
+    case 9: reg_op_over<9>(x, U, next); break;
+    case 10: reg_op_over<10>(x, U, next); break;
+    case 11: reg_op_over<11>(x, U, next); break;
+    case 12: reg_op_over<12>(x, U, next); break;
+    case 13: reg_op_over<13>(x, U, next); break;
+    default: reg_op_over<14>(x, U, next); break;
     }
 }
 
@@ -779,52 +801,68 @@ template <int B> __device__ __forceinline__ Layout layout_of(const BlkStage &stg
         l.so[j] = slot8(1u << stg.pos[j]);
     return l;
 }
-// Load and store phase: member `it` is local index threadIdx.x + it 2^(B-4).
-template <int B> __device__ __forceinline__ Layout layout_lines()
+// Load and store phase: member `it` is local index threadIdx.x + it 2^(nb-4).
+__device__ __forceinline__ Layout layout_lines(int nb)
 {
     Layout l;
     l.s0 = slot8(threadIdx.x);
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-        l.so[j] = slot8(1u << (B - 4 + j));
+        l.so[j] = slot8(1u << (nb - 4 + j));
     return l;
 }
-// From one layout to another. The slots of the first were the thread's own (or nobody's).
-__device__ __forceinline__ void through_lds(double *s, double2 (&x)[16], const Layout &from, const Layout &to)
+// From one layout to another, of the threads that hold amplitudes. The slots of the first were the thread's own (or
+// nobody's).
+__device__ __forceinline__ void through_lds(double *s, double2 (&x)[16], const Layout &from, const Layout &to,
+                                            bool act = true)
 {
+    if (act) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
-        s[from(r)] = x[r].x;
+        for (int r = 0; r < 16; ++r)
+            s[from(r)] = x[r].x;
+    }
     lds_barrier();
+    if (act) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
-        x[r].x = s[to(r)];
+        for (int r = 0; r < 16; ++r)
+            x[r].x = s[to(r)];
+    }
     lds_barrier();
+    if (act) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
-        s[from(r)] = x[r].y;
+        for (int r = 0; r < 16; ++r)
+            s[from(r)] = x[r].y;
+    }
     lds_barrier();
+    if (act) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
-        x[r].y = s[to(r)];
+        for (int r = 0; r < 16; ++r)
+            x[r].y = s[to(r)];
+    }
 }
 template <int B>
 __device__ __forceinline__ Layout run_stages(double *s, double2 (&x)[16], Layout at, const BlkStage *__restrict__ stages,
-                                             int nstages, const double *__restrict__ mats)
+                                             int nstages, const double *__restrict__ mats, bool act = true)
 {
     for (int t = 0; t < nstages; ++t) {
         const BlkStage &stg = stages[t];
         const Layout to = layout_of<B>(stg);
-        through_lds(s, x, at, to);
+        through_lds(s, x, at, to, act);
         at = to;
         uint32_t moff = stg.mat_base;
         const uint32_t masks = stg.masks;
         const int nops = stg.nops;
+        // the next record's lines, while this stage's arithmetic runs
+        typedef const __attribute__((address_space(4))) uint32_t *cwords;
+        cwords w = (cwords)(stages + (t + 1 < nstages ? t + 1 : t));
+        const uint32_t l0 = w[0], l1 = w[16], l2 = w[sizeof(BlkStage) / 4 - 1];
         for (int o = 0; o < nops; ++o) {
             const int mask = (int)(masks >> (4 * o)) & 15;
-            reg_op_over_dispatch(x, mask, mats + moff);
-            moff += 2u << (2 * __builtin_popcount(mask));
+            const uint32_t size = 2u << (2 * __builtin_popcount(mask));
+            reg_op_over_dispatch(x, mask, mats + moff, mats + moff + size);
+            moff += size;
         }
+        asm volatile("" ::"s"(l0), "s"(l1), "s"(l2));
     }
     return at;
 }
@@ -857,8 +895,8 @@ __global__ __launch_bounds__(1 << (B - 4), 4) void k_block_c128(double2 *__restr
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     warm_scalar(stages, nstages * (uint32_t)sizeof(BlkStage), wave, T >= 64 ? T / 64 : 1);
     warm_scalar(mats + warm_at, warm, wave, T >= 64 ? T / 64 : 1);
-    const Layout at = run_stages<B>(s, x, layout_lines<B>(), stages, nstages, mats);
-    through_lds(s, x, at, layout_lines<B>());
+    const Layout at = run_stages<B>(s, x, layout_lines(B), stages, nstages, mats);
+    through_lds(s, x, at, layout_lines(B));
 #pragma unroll
     for (int it = 0; it < 16; ++it) {
         NV *a = pb + blk_hi<4>(h, it);
@@ -1188,8 +1226,9 @@ __global__ __launch_bounds__(256) void k_block_async(typename BT<R>::C2 *__restr
 // executes pass k of every circuit that has more than k passes, all of those passes' blocks forming one flat index
 // space that the whole grid walks, so a large circuit is spread over every CU instead of one workgroup. The items of
 // a level are sorted by their first flat block; a workgroup finds the item of block g by binary search.
-//   * a SMALL item (level 0 only, placed first) is a whole circuit of at most B qubits: one workgroup initialises,
-//     evolves and measures it in LDS (FP64 probabilities written straight from LDS);
+//   * a SMALL item (placed first) is a circuit of at most B qubits, or the level's share of its stages: one workgroup
+//     initialises, evolves and measures it in LDS (FP64 probabilities written straight from LDS); between shares the
+//     state waits in memory;
 //   * any other item is one pass over a circuit of more than B qubits held in HBM: its FIRST pass generates the
 //     basis state |0..0> in registers instead of reading it, its LAST pass writes |amp|^2 in FP64 instead of the
 //     amplitudes. Passes of one circuit are ordered by the launch boundaries between levels.
@@ -1208,31 +1247,38 @@ __device__ __forceinline__ int find_item(const BatchItem *__restrict__ items, in
 }
 
 template <class R, int B>
-__device__ __forceinline__ void batch_small(typename BT<R>::C2 *s, const BatchItem &it, double *__restrict__ prob_base,
-                                            const BatchPass *__restrict__ passes, const BlkStage *__restrict__ stages,
-                                            const R *__restrict__ mats)
+__device__ __forceinline__ void batch_small(typename BT<R>::C2 *s, const BatchItem &it,
+                                            typename BT<R>::C2 *__restrict__ psi_base, double *__restrict__ prob_base,
+                                            const BlkStage *__restrict__ stages, const R *__restrict__ mats)
 {
     using C2 = typename BT<R>::C2;
     const uint32_t N = 1u << it.n;
+    C2 *psi = psi_base + it.state_off;
     for (uint32_t m = threadIdx.x; m < N; m += blockDim.x) {
         C2 v;
-        v.x = m == 0 ? (R)1 : (R)0;
-        v.y = 0;
+        if (it.flags & kBatchFirst) {
+            v.x = m == 0 ? (R)1 : (R)0;
+            v.y = 0;
+        } else {
+            v = psi[m];
+        }
         s[swz(m)] = v;
     }
     lds_barrier();
-    for (int p = 0; p < it.npass; ++p) {
-        const BatchPass &bp = passes[it.pass + p];
-        for (int t = 0; t < bp.nstages; ++t) {
-            run_stage_n<R>(s, stages[bp.stage_begin + t], mats, it.n);
-            lds_barrier();
-        }
+    for (int t = 0; t < it.nstages; ++t) {
+        run_stage_n<R>(s, stages[it.stage_begin + t], mats, it.n);
+        lds_barrier();
     }
-    double *out = prob_base + it.prob_off;
-    for (uint32_t m = threadIdx.x; m < N; m += blockDim.x) {
-        const C2 v = s[swz(m)];
-        const double re = (double)v.x, im = (double)v.y;
-        out[m] = re * re + im * im;
+    if (it.flags & kBatchLast) {
+        double *out = prob_base + it.prob_off;
+        for (uint32_t m = threadIdx.x; m < N; m += blockDim.x) {
+            const C2 v = s[swz(m)];
+            const double re = (double)v.x, im = (double)v.y;
+            out[m] = re * re + im * im;
+        }
+    } else {
+        for (uint32_t m = threadIdx.x; m < N; m += blockDim.x)
+            psi[m] = s[swz(m)];
     }
     lds_barrier();
 }
@@ -1328,7 +1374,7 @@ __global__ __launch_bounds__(256, (sizeof(R) == 4 ? 4 : 1)) void k_batch_level(t
         cur = items[find_item(items, nitems, g)];
         if (!(cur.flags & kBatchSmall))
             break;
-        batch_small<R, B>(s, cur, prob_base, passes, stages, mats);
+        batch_small<R, B>(s, cur, psi_base, prob_base, stages, mats);
     }
     if (g >= nblocks)
         return;
@@ -1363,6 +1409,11 @@ __global__ __launch_bounds__(256, (sizeof(R) == 4 ? 4 : 1)) void k_batch_level(t
     const BatchPass *bp = &passes[cur.pass];
     uint64_t base = ins0b(g - cur.blk_begin, bp->outer) | spread(threadIdx.x, bp->bm);
     batch_fetch<R, B>(pre, psi_base + cur.state_off, base, bp->bm);
+    {
+        const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), len = cur.mat_end - cur.mat_begin;
+        warm_scalar(stages + cur.stage_begin, cur.nstages * (uint32_t)sizeof(BlkStage), wave, 4);
+        warm_scalar(mats + cur.mat_begin, (len < kWarmMax / sizeof(R) ? len * (uint32_t)sizeof(R) : kWarmMax), wave, 4);
+    }
     mfetch(bp);
     batch_to_lds<R, B>(s, pre, base, bp->bm, (cur.flags & kBatchFirst) != 0, sbase);
     mstore(bp);
@@ -1428,24 +1479,113 @@ __global__ __launch_bounds__(256, (sizeof(R) == 4 ? 4 : 1)) void k_batch_level(t
     }
 }
 
+// Complex128: the items of a level on the register stages of k_block_c128, four workgroups a CU. A small item's
+// amplitudes are those of the first 2^(n-4) threads. With a few blocks a CU, each of another circuit, a block is a chain
+// of waits for its tables: a 2-qubit matrix is read whole, once, and the next matrix and stage record are fetched ahead
+// (24 circuits of 10 to 20 qubits 803 us; matrices row by row, not ahead, 1005; two workgroups a CU with the next
+// block's loads in registers 996).
+template <int B, bool NT>
+__global__ __launch_bounds__(1 << (B - 4), 4) void k_batch_c128(double2 *__restrict__ psi_base,
+                                                                double *__restrict__ prob_base,
+                                                                const BatchItem *__restrict__ items, int nitems,
+                                                                uint32_t nblocks, const BatchPass *__restrict__ passes,
+                                                                const BlkStage *__restrict__ stages,
+                                                                const double *__restrict__ mats)
+{
+    using NV = NT2<double>::type;
+    constexpr int T = 1 << (B - 4);
+    extern __shared__ __align__(16) unsigned char smem_blk[];
+    double *s = reinterpret_cast<double *>(smem_blk);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (uint32_t g = blockIdx.x; g < nblocks; g += gridDim.x) {
+        const BatchItem it = items[find_item(items, nitems, g)];
+        const bool small = it.flags & kBatchSmall;
+        const int nb = small ? it.n : B;
+        const bool act = threadIdx.x < (1u << (nb - 4));
+        const BatchPass &bp = passes[it.pass];
+        uint64_t h[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            h[j] = (uint64_t)1 << (small ? nb - 4 + j : bp.bm.lpos[B - 4 + j]);
+        uint64_t own = threadIdx.x;
+        if (!small)
+            own = ins0b(g - it.blk_begin, bp.outer) | spread(threadIdx.x, bp.bm);
+        NV *const pb = reinterpret_cast<NV *>(psi_base + it.state_off + own);
+        double2 x[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            x[r] = double2{0, 0};
+        if (it.flags & kBatchFirst) {
+            x[0].x = own == 0 ? 1.0 : 0.0;
+        } else if (act) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const NV *a = pb + blk_hi<4>(h, r);
+                const NV v = NT ? __builtin_nontemporal_load(a) : *a;
+                x[r].x = v.x;
+                x[r].y = v.y;
+            }
+        }
+        const uint32_t len = it.mat_end - it.mat_begin;
+        warm_scalar(stages + it.stage_begin, it.nstages * (uint32_t)sizeof(BlkStage), wave, T / 64);
+        warm_scalar(mats + it.mat_begin, len < kWarmMax / 8 ? len * 8 : kWarmMax, wave, T / 64);
+        if (g != blockIdx.x)
+            lds_barrier();  // the last item's slots have been read
+        const Layout lines = layout_lines(nb);
+        const Layout at = run_stages<B>(s, x, lines, stages + it.stage_begin, it.nstages, mats, act);
+        through_lds(s, x, at, lines, act);
+        if (!act)
+            continue;
+        if (it.flags & kBatchLast) {
+            double *out = prob_base + it.prob_off + own;
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                out[blk_hi<4>(h, r)] = x[r].x * x[r].x + x[r].y * x[r].y;
+        } else {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                NV *a = pb + blk_hi<4>(h, r);
+                NV v;
+                v.x = x[r].x;
+                v.y = x[r].y;
+                if constexpr (NT)
+                    __builtin_nontemporal_store(v, a);
+                else
+                    *a = v;
+            }
+        }
+    }
+}
+
 template <class R, int B>
 hipError_t batch_b(void *psi, double *probs, const BatchItem *items, int nitems, uint32_t nblocks,
                    const BatchPass *passes, const BlkStage *stages, const void *mats,
                    int wg_per_cu, hipStream_t s)
 {
     using C2 = typename BT<R>::C2;
-    // complex64: room for a pass's fused stage matrices next to the block
-    const size_t shm = (sizeof(C2) << B) + (sizeof(R) == 4 ? 256 * sizeof(C2) * kMaxMfmaStages : 0);
-    if (hipError_t e = qs_allow_lds((const void *)k_batch_level<R, B>, shm))
-        return e;
     uint64_t grid = (uint64_t)qs_cu_count() * wg_per_cu;
     if (grid > nblocks)
         grid = nblocks;
     if (grid == 0)
         return hipSuccess;
-    hipLaunchKernelGGL((k_batch_level<R, B>), dim3((unsigned)grid), dim3(256), shm, s, (C2 *)psi, probs, items, nitems,
-                       nblocks, passes, stages, (const R *)mats);
-    return hipGetLastError();
+    if constexpr (sizeof(R) == 8) {
+        auto go = [&](auto kernel) {
+            if (hipError_t e = qs_allow_lds((const void *)kernel, (size_t)8 << B))
+                return e;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(1 << (B - 4)), (size_t)8 << B, s, (double2 *)psi, probs,
+                               items, nitems, nblocks, passes, stages, (const double *)mats);
+            return hipGetLastError();
+        };
+        return qs_streams(((uint64_t)nblocks << B) * 16) ? go(k_batch_c128<B, true>) : go(k_batch_c128<B, false>);
+    } else {
+        // room for a pass's fused stage matrices next to the block
+        const size_t shm = (sizeof(C2) << B) + 256 * sizeof(C2) * kMaxMfmaStages;
+        if (hipError_t e = qs_allow_lds((const void *)k_batch_level<R, B>, shm))
+            return e;
+        hipLaunchKernelGGL((k_batch_level<R, B>), dim3((unsigned)grid), dim3(256), shm, s, (C2 *)psi, probs, items, nitems,
+                           nblocks, passes, stages, (const R *)mats);
+        return hipGetLastError();
+    }
 }
 
 template <class R>
@@ -1510,11 +1650,12 @@ hipError_t block_b(void *psi, uint64_t nblocks, const InsBits &outer, const Bloc
     // persistent workgroups (each walks several blocks so its loads can run ahead of its arithmetic)
     const uint64_t cus = (uint64_t)qs_cu_count();
     const uint64_t grid = block_grid_nt(NT, nblocks);
-    // four blocks a CU and more: the kernel that keeps four there. Fewer are a question of latency, and one barrier a
-    // stage takes less of it than three (12-qubit blocks, microseconds a pass of SU(4) layers: 19 qubits 20.4 against
-    // 25.2, 21 qubits 26.7 against 31.5, 22 qubits 50.5 against 49.8, 24 qubits 180 against 174).
+    // Four workgroups of 256 threads a CU and more: the kernel that keeps four there. Fewer are a question of latency,
+    // and one barrier a stage takes less of it than three (microseconds a pass of SU(4) layers: 12-qubit blocks 20
+    // qubits 22.4 against 27.3, 21 qubits 26.7 against 31.5, 22 qubits 50.5 against 47.4, 24 qubits 180 against 174;
+    // 10-qubit blocks 21 qubits 24.2 against 27.4, 22 qubits 42.5 against 41.6).
     if constexpr (B >= 10 && W == 4 && sizeof(R) == 8) {
-        if (nblocks >= 4 * (uint64_t)qs_cu_count() && !lstages && !qs_tunables().block_async) {
+        if (nblocks << B >= (uint64_t)qs_cu_count() << 14 && !lstages && !qs_tunables().block_async) {
             const bool nt = qs_streams((nblocks << B) * 16);
             auto go = [&](auto kernel) {
                 if (hipError_t e = qs_allow_lds((const void *)kernel, (size_t)8 << B))

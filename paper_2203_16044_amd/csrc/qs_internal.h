@@ -292,23 +292,27 @@ struct BatchCirc {
     uint64_t prob_off;   // offset of its 2^n FP64 probabilities
     int n;
     int pass_begin, npass;
+    int stage_begin, nstages;     // of all its passes
+    uint32_t mat_begin, mat_end;
 };
 struct BatchPass {
     InsBits outer;  // block number -> base index (zeros at the local positions)
     BlockMap bm;
     int stage_begin, nstages;
     BlkMfma mf;     // complex64: the pass's fused stage matrices (pool offsets in the batch's pool)
+    uint32_t mat_begin, mat_end;
 };
-// one work item of a level: a whole small circuit in LDS, or one pass of a circuit held in HBM
-constexpr int kBatchFirst = 1;  // first pass: generate |0..0> instead of reading the state
-constexpr int kBatchLast = 2;   // last pass: write FP64 probabilities instead of amplitudes
-constexpr int kBatchSmall = 4;  // whole circuit of at most B qubits, one workgroup, in LDS
+// one work item of a level: a share of the stages of a small circuit, in LDS, or one pass of a circuit held in HBM
+constexpr int kBatchFirst = 1;  // first pass or share: generate |0..0> instead of reading the state
+constexpr int kBatchLast = 2;   // last: write FP64 probabilities instead of amplitudes
+constexpr int kBatchSmall = 4;  // circuit of at most B qubits, one workgroup
 struct BatchItem {
-    uint64_t state_off;  // amplitude offset of the circuit's HBM state
+    uint64_t state_off;  // amplitude offset of the circuit's state (small: where it waits between levels)
     uint64_t prob_off;   // offset of its 2^n FP64 probabilities
     uint32_t blk_begin;  // first flat block of the item within its level (small items take one block)
-    int pass;            // global index of the item's pass (small: of its first pass)
-    int npass;           // small: number of passes; otherwise 1
+    int pass;            // global index of the item's pass (not small)
+    int stage_begin, nstages;
+    uint32_t mat_begin, mat_end;  // their matrices in the pool (real elements)
     int n;
     int flags;
 };

@@ -1853,6 +1853,7 @@ struct qs_batch {
     std::vector<int> level_begin;      // items of level k: [level_begin[k], level_begin[k + 1])
     std::vector<uint32_t> level_blocks;
     uint64_t state_amps = 0, prob_count = 0;
+    uint64_t parked_amps = 0;  // behind the states: small circuits between levels
     bool finalized = false;
     void *psi = nullptr;
     double *probs = nullptr;
@@ -1901,7 +1902,7 @@ int batch_upload(qs_batch *Bt)
 {
     const size_t esz = Bt->dtype == QS_C128 ? 16 : 8;
     void *p = nullptr;
-    hipError_t e = hipMalloc(&p, std::max<uint64_t>(Bt->state_amps, 1) * esz);
+    hipError_t e = hipMalloc(&p, std::max<uint64_t>(Bt->state_amps + Bt->parked_amps, 1) * esz);
     if (e != hipSuccess)
         return qs_hip_fail(e, "hipMalloc(batch states)");
     Bt->psi = p;
@@ -1916,13 +1917,18 @@ int batch_upload(qs_batch *Bt)
         return rc;
     if (int rc = upload_vec(&Bt->dstages, Bt->stages))
         return rc;
+    // 64 zero elements past the end, as in a plan's pool: slack for lines that the kernels fetch ahead
+    const size_t npool = Bt->pool.size() + 64;
     if (Bt->dtype == QS_C128) {
+        std::vector<double> m(Bt->pool.begin(), Bt->pool.end());
+        m.resize(npool, 0.0);
         double *d = nullptr;
-        if (int rc = upload_vec(&d, Bt->pool))
+        if (int rc = upload_vec(&d, m))
             return rc;
         Bt->dmats = d;
     } else {
         std::vector<float> f(Bt->pool.begin(), Bt->pool.end());
+        f.resize(npool, 0.0f);
         float *d = nullptr;
         if (int rc = upload_vec(&d, f))
             return rc;
@@ -2037,8 +2043,14 @@ QS_API int qs_batch_add(qs_batch *Bt, const qs_circuit *c)
         bp.mf = pp.mf;
         for (int i = 0; i < bp.mf.n; ++i)
             bp.mf.off[i] += m0;
+        bp.mat_begin = m0 + pp.mat_begin;
+        bp.mat_end = m0 + pp.mat_end;
         Bt->passes.push_back(bp);
     }
+    bc.stage_begin = s0;
+    bc.nstages = (int)P->stages.size();
+    bc.mat_begin = m0;
+    bc.mat_end = m0 + (uint32_t)P->pool.size();
     if (P->passes.empty() && c->n > Bt->b) {
         // a circuit held in HBM needs one pass to initialise and measure its state: an empty one over the low qubits
         BatchPass bp{};
@@ -2074,8 +2086,11 @@ QS_API int qs_batch_finalize(qs_batch *Bt)
         return QS_OK;
     if (Bt->pool.size() >= ((size_t)1 << 32))
         return qs_fail(QS_EUNSUPPORTED, "qs_batch_finalize: matrix pool too large");
-    // Level k holds pass k of every circuit kept in HBM; level 0 also holds the circuits that live in LDS, costliest
-    // first, ahead of all blocks so that they start at once.
+    // Level k holds pass k of every circuit kept in HBM. The circuits that fit LDS come ahead of all blocks, costliest
+    // first, so that they start at once: each one workgroup's chain of stages, which in one piece would hold up level 0
+    // (24 circuits of 10 to 20 qubits complex128: 210 us of the 1050; 40 of 10 to 17 complex64: 188 of 557), they are
+    // dealt out over the levels, their states waiting in memory in between. Where they are more than the compute units
+    // they are no chain but the work itself, and stay in one piece.
     std::vector<int> small, large;
     int nlev = 0;
     for (int i = 0; i < (int)Bt->circs.size(); ++i) {
@@ -2092,24 +2107,42 @@ QS_API int qs_batch_finalize(qs_batch *Bt)
         return std::ldexp(1.0 + Bt->nops[a], Bt->circs[a].n) > std::ldexp(1.0 + Bt->nops[b], Bt->circs[b].n);
     });
     std::stable_sort(large.begin(), large.end(), [&](int a, int b) { return Bt->circs[a].n > Bt->circs[b].n; });
+    constexpr int kDealStages = 4;  // a share: a load and a store of the state are worth about one stage
+    const bool deal = nlev > 1 && (int)small.size() <= qs_cu_count();
+    std::vector<uint64_t> parked(small.size(), 0);
+    Bt->parked_amps = 0;
+    if (deal)
+        for (size_t j = 0; j < small.size(); ++j) {
+            parked[j] = Bt->state_amps + Bt->parked_amps;
+            Bt->parked_amps += (uint64_t)1 << Bt->circs[small[j]].n;
+        }
     Bt->items.clear();
     Bt->level_begin.clear();
     Bt->level_blocks.clear();
     for (int lev = 0; lev < nlev; ++lev) {
         Bt->level_begin.push_back((int)Bt->items.size());
         uint64_t blk = 0;
-        if (lev == 0)
-            for (int i : small) {
-                const BatchCirc &c = Bt->circs[i];
-                Bt->items.push_back(BatchItem{0, c.prob_off, (uint32_t)blk, c.pass_begin, c.npass, c.n, kBatchSmall});
-                blk += 1;
-            }
+        for (size_t j = 0; j < small.size(); ++j) {
+            const BatchCirc &c = Bt->circs[small[j]];
+            const int parts = deal ? std::max(1, std::min(nlev, (c.nstages + kDealStages - 1) / kDealStages)) : 1;
+            if (lev >= parts)
+                continue;
+            const int a = (int)((int64_t)c.nstages * lev / parts), e = (int)((int64_t)c.nstages * (lev + 1) / parts);
+            const int flags = kBatchSmall | (lev == 0 ? kBatchFirst : 0) | (lev == parts - 1 ? kBatchLast : 0);
+            Bt->items.push_back(BatchItem{
+                parked[j], c.prob_off, (uint32_t)blk, 0, c.stage_begin + a, e - a,
+                a < c.nstages ? Bt->stages[c.stage_begin + a].mat_base : c.mat_end,
+                e < c.nstages ? Bt->stages[c.stage_begin + e].mat_base : c.mat_end, c.n, flags});
+            blk += 1;
+        }
         for (int i : large) {
             const BatchCirc &c = Bt->circs[i];
             if (c.npass <= lev)
                 continue;
             const int flags = (lev == 0 ? kBatchFirst : 0) | (lev == c.npass - 1 ? kBatchLast : 0);
-            Bt->items.push_back(BatchItem{c.state_off, c.prob_off, (uint32_t)blk, c.pass_begin + lev, 1, c.n, flags});
+            const BatchPass &bp = Bt->passes[c.pass_begin + lev];
+            Bt->items.push_back(BatchItem{c.state_off, c.prob_off, (uint32_t)blk, c.pass_begin + lev, bp.stage_begin,
+                                          bp.nstages, bp.mat_begin, bp.mat_end, c.n, flags});
             blk += (uint64_t)1 << (c.n - Bt->b);
         }
         if (blk >= ((uint64_t)1 << 31))
