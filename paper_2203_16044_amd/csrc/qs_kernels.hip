@@ -1094,9 +1094,81 @@ hipError_t fswap_t(void *psi_, int n, int lo, int hi, int s_, hipStream_t s)
 }
 }  // namespace
 
+namespace {
+// A fused-swap within the lowest index bits: 32 KiB of consecutive amplitudes per workgroup, read and written as
+// 16-byte vectors, permuted in LDS. (As tiles of 2^s x 2^s runs it left a workgroup as little as 64 bytes: qubits 1 and 2
+// of 27, complex64, 5741 us; 362 this way, as any swap of the kind. With more to a tile it moved 8 bytes a lane: 509.) The slots of higher bits
+// are folded onto the banks, in pairs for complex64, so that a transposition's columns are spread over them.
+template <class R> struct FswTile;
+template <> struct FswTile<double> { static constexpr int B = 11; };
+template <> struct FswTile<float> { static constexpr int B = 12; };
+template <class R> __device__ __forceinline__ uint32_t fsw_slot(uint32_t i)
+{
+    return sizeof(R) == 8 ? i ^ (((i >> 4) ^ (i >> 8)) & 15u) : i ^ (((i >> 5) ^ (i >> 9)) & 30u);
+}
+template <class R, bool NT>
+__global__ __launch_bounds__(256) void k_fswap_tile(typename LaneVec<R>::T *__restrict__ psi, int lo, int hi, uint32_t sm)
+{
+    using V = typename LaneVec<R>::T;
+    using C2 = typename CT<R>::T;
+    constexpr int P = sizeof(R) == 8 ? 1 : 2, N = 1 << FswTile<R>::B, PER = N / P / 256;
+    __shared__ __align__(16) C2 s[N];
+    V *p = psi + (uint64_t)blockIdx.x * (N / P);
+    V x[PER];
+#pragma unroll
+    for (int it = 0; it < PER; ++it) {
+        const V *a = p + threadIdx.x + 256 * it;
+        x[it] = NT ? __builtin_nontemporal_load(a) : *a;
+    }
+#pragma unroll
+    for (int it = 0; it < PER; ++it)
+        *reinterpret_cast<V *>(&s[fsw_slot<R>((threadIdx.x + 256 * it) * P)]) = x[it];
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < PER; ++it) {
+        const uint32_t i = (threadIdx.x + 256 * it) * P;
+#pragma unroll
+        for (int h = 0; h < P; ++h) {
+            const C2 z = s[fsw_slot<R>((uint32_t)fsw_sigma(i + h, lo, hi, sm))];
+            x[it][2 * h] = z.x;
+            x[it][2 * h + 1] = z.y;
+        }
+        V *a = p + i / P;
+        if constexpr (NT)
+            __builtin_nontemporal_store(x[it], a);
+        else
+            *a = x[it];
+    }
+}
+template <class R> hipError_t fswap_tile(void *psi, int n, int lo, int hi, int s_, hipStream_t s)
+{
+    using V = typename LaneVec<R>::T;
+    const dim3 g((unsigned)((uint64_t)1 << (n - FswTile<R>::B))), b(256);
+    const uint32_t sm = (1u << s_) - 1u;
+    if (qs_streams(((uint64_t)1 << n) * sizeof(typename CT<R>::T)))
+        hipLaunchKernelGGL((k_fswap_tile<R, true>), g, b, 0, s, (V *)psi, lo, hi, sm);
+    else
+        hipLaunchKernelGGL((k_fswap_tile<R, false>), g, b, 0, s, (V *)psi, lo, hi, sm);
+    return hipGetLastError();
+}
+}  // namespace
+
+// Swaps within one line and the lowest bits go tile by tile (from lo on that is a whole line, moving the exchanged runs
+// alone is less; complex128 states streaming from HBM only up to bit 6: 27 qubits, lo 0, s 3, hi 3 1189 us against 789,
+// but s 4, hi 4 725 against 787). Complex64 swaps that leave bit 0 alone move pairs of amplitudes, as complex128 amplitudes of a state of
+// one qubit less: 16 bytes a lane (27 qubits, lo 1 to 3, hi far above: 510 us, so 380; 25 qubits, in cache, 84 and 65).
+// Whole lines streaming from HBM are the exception: 8 bytes a lane are 5 to 10 % faster (27 qubits, lo 4, s 1: 178 and 195).
 hipError_t launch_fused_swap(int dtype, void *psi, int n, int lo, int hi, int s_, hipStream_t s)
 {
-    return dtype == QS_C128 ? fswap_t<double2>(psi, n, lo, hi, s_, s) : fswap_t<float2>(psi, n, lo, hi, s_, s);
+    if (dtype == QS_C128)
+        return lo < 3 && hi + s_ <= (qs_streams((uint64_t)16 << n) ? 6 : FswTile<double>::B) && n >= FswTile<double>::B
+                   ? fswap_tile<double>(psi, n, lo, hi, s_, s)
+                   : fswap_t<double2>(psi, n, lo, hi, s_, s);
+    if (lo < 4 && hi + s_ <= FswTile<float>::B && n >= FswTile<float>::B)
+        return fswap_tile<float>(psi, n, lo, hi, s_, s);
+    if (lo >= 1 && (lo < 4 || !qs_streams((uint64_t)8 << n)))
+        return fswap_t<double2>(psi, n - 1, lo - 1, hi - 1, s_, s);
+    return fswap_t<float2>(psi, n, lo, hi, s_, s);
 }
 
 int probs_blocks(uint64_t dim)
