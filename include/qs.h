@@ -356,8 +356,8 @@ QS_API int qs_mlp_train_step(qs_mlp *m, const float *X, const float *T, int B, f
  * Many circuits (8..30 qubits each, gates on at most 3 qubits, no fused-swaps) run as one short sequence of
  * persistent launches, one per pass level: launch k runs pass k of every circuit that has more than k block passes,
  * all of their blocks forming one index space that the whole grid walks (so a large circuit is spread over every
- * compute unit). Circuits of at most block_bits qubits run start to finish inside one workgroup's LDS during the
- * first launch. Every circuit starts in |0..0>, generated in the first pass, and its last pass writes its FP64
+ * compute unit). Circuits of at most block_bits qubits are one workgroup's work each, in LDS; up to as many as there
+ * are compute units, their stages are dealt out over the launches. Every circuit starts in |0..0>, generated in the first pass, and its last pass writes its FP64
  * output probabilities instead of amplitudes.
  *   block_bits 10..12 (the LDS block), low_bits the always-local low qubits, wg_per_cu 1..64 persistent
  *   workgroups per compute unit (tile and schedule parameters chosen by the autotuner). */
