@@ -53,13 +53,20 @@ template <class T> __device__ __forceinline__ void st(T *p, T v, int nt)
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// dense k-qubit gate, k <= 3: the group's 2^k members live in registers; U comes from kernel arguments.
+// dense k-qubit gate, k <= 3 (and complex128 k = 4 where it streams whole lines, dense_k): the group's 2^k members live in
+// registers; U comes from kernel arguments, for k = 4 from device memory through uniform (scalar) loads.
 // ---------------------------------------------------------------------------------------------------------
 template <class R, int K> struct MatByVal {
     R v[2 << (2 * K)];
     __device__ __forceinline__ R re(int i) const { return v[2 * i]; }
     __device__ __forceinline__ R im(int i) const { return v[2 * i + 1]; }
 };
+template <class R> struct MatByPtr {
+    const R *__restrict__ p;
+    __device__ __forceinline__ R re(int i) const { return p[2 * i]; }
+    __device__ __forceinline__ R im(int i) const { return p[2 * i + 1]; }
+};
+
 // ---------------------------------------------------------------------------------------------------------
 // 1-qubit gate whose target lies inside a wave's contiguous span (complex128: q < 6; complex64: q < 7). Every lane
 // streams one 16-byte vector (one complex128 amplitude, or two adjacent complex64 ones) with full-width coalesced
@@ -883,6 +890,16 @@ hipError_t dense_k(void *psi, uint64_t ngroups, const InsBits &ins, const TPos &
                                (C2 *)psi, ngroups, ins, tp, m, tu.nontemporal);
         }
     } else {
+        // complex128 k = 4 from HBM with no target inside a 128-byte line: groups in registers, which depend less on
+        // where the targets lie than the tiles do (27 qubits, targets 5 9 13 20: 765 us against 929, 4 8 15 24: 763
+        // against 814, 10 12 17 23: 766 against 699; SU(4) layers in 4-qubit blocks 770 against 820 a pass). In cache
+        // (24 qubits: 111 against 95) and with low targets (0 6 11 22: 860 against 743) the tiles are the better form.
+        if constexpr (K == 4 && sizeof(R) == 8)
+            if (qs_streams((ngroups << ins.np) * sizeof(C2)) && tp.tpos[0] >= 3) {
+                hipLaunchKernelGGL((k_dense<R, 4, 1, MatByPtr<R>>), dim3(grid_for(ngroups, bs)), dim3(bs), 0, s, (C2 *)psi,
+                                   ngroups, ins, tp, MatByPtr<R>{(const R *)Ud}, tu.nontemporal);
+                return hipGetLastError();
+            }
         return launch_dense_mfma(std::is_same<R, double>::value ? QS_C128 : QS_C64, K, psi, ngroups, ins, tp, Ud, s);
     }
     return hipGetLastError();

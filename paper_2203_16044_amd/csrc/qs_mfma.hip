@@ -169,11 +169,14 @@ __global__ __launch_bounds__(256) void k_dense_mfma(typename MF<R>::C2 *__restri
     };
 
     const uint64_t G = gridDim.x;
+    // k = 6 is bound by the matrix cores and loses by it (28 qubits 2255 us against 2207); k = 4, SU(4) layers on 27 qubits,
+    // 861 us a pass, so 820
+    auto at = [&](uint64_t t) { return NT && K < 6 ? (uint64_t)xcd_runs((uint32_t)t, ntiles) : t; };
     uint64_t T = blockIdx.x;
     if (T >= ntiles)
         return;
     pair_t pre[LPT];
-    uint64_t base = qs_ins0(T * (16 * CT), ins);
+    uint64_t base = qs_ins0(at(T) * (16 * CT), ins);
 #pragma unroll
     for (int it = 0; it < LPT; ++it) {
         pre[it] = pair_t(0);
@@ -187,7 +190,7 @@ __global__ __launch_bounds__(256) void k_dense_mfma(typename MF<R>::C2 *__restri
     for (;;) {
         const uint64_t Tn = T + G;
         const bool more = WHOLE && Tn < ntiles;  // uniform
-        const uint64_t nbase = qs_ins0((more ? Tn : T) * (16 * CT), ins);
+        const uint64_t nbase = qs_ins0(at(more ? Tn : T) * (16 * CT), ins);
         if (more) {
 #pragma unroll
             for (int it = 0; it < LPT; ++it)
