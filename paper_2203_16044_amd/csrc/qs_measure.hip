@@ -8,7 +8,7 @@
 //    from coalesced loads, a deterministic two-level scan turns the chunk masses into an inclusive prefix, and each
 //    shot (one wave) finds its chunk by a 64-ary search and its index by two wave scans over the chunk's probabilities
 //    held in LDS. Shot k returns the smallest index i whose cumulative mass exceeds u_k x total mass, up to the
-//    rounding of the sums; an index without mass is never returned.
+//    rounding of the sums; where there is mass, an index without it is never returned.
 #include <cmath>
 #include <cstring>
 
@@ -238,13 +238,17 @@ __global__ __launch_bounds__(256) void k_chunk_mass(const typename MVec<R>::T *_
         mass[c] = s;
 }
 
-// Level 1 of the prefix scan: each workgroup scans a tile of kTile masses (8 sequential per thread, then an LDS
-// Hillis-Steele scan of the 256 thread sums) into tile-local inclusive prefixes, in place, and writes the tile total.
+// Level 1 of the prefix scan: each workgroup scans a tile of kTile masses (8 sequential per thread, then the threads' runs
+// joined two by two) into tile-local inclusive prefixes, in place, and writes the tile total, its last prefix. Where two
+// runs join, the left one's last prefix is added to every prefix of the right one, so that the prefix never falls and
+// stays exactly where a chunk has no mass: a target cannot meet an empty chunk. (Prefixes and thread sums added up in
+// different orders rise and fall by a rounding at such chunks.)
 __global__ __launch_bounds__(256) void k_scan_tile(double *__restrict__ io, uint64_t len,
                                                    double *__restrict__ totals)
 {
-    __shared__ double sh[256];
-    const uint64_t base = (uint64_t)blockIdx.x * kTile + (uint64_t)threadIdx.x * 8;
+    __shared__ double last[256];  // each thread's last prefix
+    const int t = threadIdx.x;
+    const uint64_t base = (uint64_t)blockIdx.x * kTile + (uint64_t)t * 8;
     double v[8];
     double run = 0.0;
 #pragma unroll
@@ -253,21 +257,24 @@ __global__ __launch_bounds__(256) void k_scan_tile(double *__restrict__ io, uint
         run += v[j];
         v[j] = run;
     }
-    sh[threadIdx.x] = run;
+    last[t] = run;
     __syncthreads();
-    for (int d = 1; d < 256; d <<= 1) {
-        const double y = (int)threadIdx.x >= d ? sh[threadIdx.x - d] : 0.0;
-        __syncthreads();
-        sh[threadIdx.x] += y;
+    for (int d = 1; d < 256; d <<= 1) {  // read: threads with bit d clear; written: threads with it set
+        if (t & d) {
+            const double left = last[(t & ~(2 * d - 1)) + d - 1];
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                v[j] += left;
+            last[t] = v[7];
+        }
         __syncthreads();
     }
-    const double before = threadIdx.x > 0 ? sh[threadIdx.x - 1] : 0.0;
 #pragma unroll
     for (int j = 0; j < 8; ++j)
         if (base + j < len)
-            io[base + j] = before + v[j];
-    if (threadIdx.x == 255)
-        totals[blockIdx.x] = sh[255];
+            io[base + j] = v[j];
+    if (t == 255)
+        totals[blockIdx.x] = v[7];
 }
 
 // Level 2: the tile totals become exclusive tile offsets, totals[ntiles] their sum. The additions run in sequence (so
