@@ -133,7 +133,7 @@ QS_API int qs_fused_swap(qs_state *st, int p, int q, int s);
 
 /*
  * qs_probs -- out_dev[i] = |a_i|^2 in FP64 (complex64 components are widened first) (Sec. II-A).
- *   out_dev   device buffer of 2^n doubles (caller-owned), or NULL to compute only the norm.
+ *   out_dev   device buffer of 2^n doubles (caller-owned, 8-byte aligned), or NULL to compute only the norm.
  *   norm_out  host pointer, or NULL. When non-NULL the call synchronises the stream and stores
  *             sum_i |a_i|^2, reduced in FP64 in a fixed order (run-to-run bit-identical).
  * Errors: QS_EINVAL (st NULL), QS_EDEVICE.

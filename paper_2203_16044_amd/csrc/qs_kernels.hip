@@ -648,7 +648,7 @@ __global__ __launch_bounds__(256) void k_probs(const typename LaneVec<R>::T *__r
                                                double *__restrict__ out, double *__restrict__ partials)
 {
     using V = typename LaneVec<R>::T;
-    typedef double D2 __attribute__((ext_vector_type(2)));
+    typedef double D2 __attribute__((ext_vector_type(2), aligned(8)));  // out is any array of doubles
     constexpr int U = 4;
     __shared__ double red[256];
     double s = 0.0, c = 0.0;
