@@ -359,8 +359,9 @@ QS_API int qs_mlp_train_step(qs_mlp *m, const float *X, const float *T, int B, f
  * compute unit). Circuits of at most block_bits qubits are one workgroup's work each, in LDS; up to as many as there
  * are compute units, their stages are dealt out over the launches. Every circuit starts in |0..0>, generated in the first pass, and its last pass writes its FP64
  * output probabilities instead of amplitudes.
- *   block_bits 10..12 (the LDS block), low_bits the always-local low qubits, wg_per_cu 1..64 persistent
- *   workgroups per compute unit (tile and schedule parameters chosen by the autotuner). */
+ *   block_bits 10..12 (the LDS block), low_bits the always-local low qubits, wg_per_cu 1..64 persistent 256-thread
+ *   workgroups per compute unit, smaller ones scaled up proportionally (tile and schedule parameters chosen by the
+ *   autotuner). */
 typedef struct qs_batch qs_batch;
 QS_API int qs_batch_create(qs_batch **out, int dtype, int block_bits, int low_bits, int wg_per_cu, void *hip_stream);
 /* Change the persistent workgroups per CU (1..64) of later runs; a captured graph is dropped (the call waits for the

@@ -13,6 +13,8 @@
 // and writes the group back: one LDS round trip and one barrier per stage instead of per op. The stage records live
 // in device memory: 4 ascending local positions, up to 8 ops as 4-bit masks of the stage positions they act on
 // (k <= 3), and the pool offset of the first op's 2^k x 2^k matrix (compute precision; the others follow in order).
+#include <algorithm>
+
 #include "qs_internal.h"
 
 namespace {
@@ -1568,29 +1570,34 @@ hipError_t batch_b(void *psi, double *probs, const BatchItem *items, int nitems,
                    int wg_per_cu, hipStream_t s)
 {
     using C2 = typename BT<R>::C2;
-    uint64_t grid = (uint64_t)qs_cu_count() * wg_per_cu;
-    if (grid > nblocks)
-        grid = nblocks;
-    if (grid == 0)
+    if (nblocks == 0)
         return hipSuccess;
-    if constexpr (sizeof(R) == 8) {
-        auto go = [&](auto kernel) {
-            if (hipError_t e = qs_allow_lds((const void *)kernel, (size_t)8 << B))
-                return e;
-            hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(1 << (B - 4)), (size_t)8 << B, s, (double2 *)psi, probs,
-                               items, nitems, nblocks, passes, stages, (const double *)mats);
-            return hipGetLastError();
-        };
-        return qs_streams(((uint64_t)nblocks << B) * 16) ? go(k_batch_c128<B, true>) : go(k_batch_c128<B, false>);
-    } else {
-        // room for a pass's fused stage matrices next to the block
-        const size_t shm = (sizeof(C2) << B) + 256 * sizeof(C2) * kMaxMfmaStages;
-        if (hipError_t e = qs_allow_lds((const void *)k_batch_level<R, B>, shm))
-            return e;
-        hipLaunchKernelGGL((k_batch_level<R, B>), dim3((unsigned)grid), dim3(256), shm, s, (C2 *)psi, probs, items, nitems,
-                           nblocks, passes, stages, (const R *)mats);
-        return hipGetLastError();
-    }
+    const uint64_t wgs = (uint64_t)qs_cu_count() * wg_per_cu;  // of 256 threads
+    // Complex128 levels of one 12-qubit block's worth per compute unit and more: the kernel that keeps four workgroups
+    // there. On fewer blocks a stage's three barriers cost more than the company gives (microseconds a batch alone, and
+    // in a stream of three: 8 circuits of 13 to 16 qubits, 10-qubit blocks 464 and 201 against 403 and 176; 6 of 10 to
+    // 18, 11-qubit blocks 352 and 145 against 323 and 134; but 24 of 10 to 20 820 and 444 against 885 and 548). A
+    // threshold of a quarter loses 4 to 14 % on batches up to 19 qubits.
+    if constexpr (sizeof(R) == 8)
+        if (((uint64_t)nblocks << B) >= (uint64_t)qs_cu_count() << 12) {
+            const uint64_t grid = std::min<uint64_t>(wgs << (12 - B), nblocks);
+            auto go = [&](auto kernel) {
+                if (hipError_t e = qs_allow_lds((const void *)kernel, (size_t)8 << B))
+                    return e;
+                hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(1 << (B - 4)), (size_t)8 << B, s, (double2 *)psi,
+                                   probs, items, nitems, nblocks, passes, stages, (const double *)mats);
+                return hipGetLastError();
+            };
+            return qs_streams(((uint64_t)nblocks << B) * 16) ? go(k_batch_c128<B, true>) : go(k_batch_c128<B, false>);
+        }
+    const uint64_t grid = std::min<uint64_t>(wgs, nblocks);
+    // complex64: room for a pass's fused stage matrices next to the block
+    const size_t shm = (sizeof(C2) << B) + (sizeof(R) == 4 ? 256 * sizeof(C2) * kMaxMfmaStages : 0);
+    if (hipError_t e = qs_allow_lds((const void *)k_batch_level<R, B>, shm))
+        return e;
+    hipLaunchKernelGGL((k_batch_level<R, B>), dim3((unsigned)grid), dim3(256), shm, s, (C2 *)psi, probs, items, nitems,
+                       nblocks, passes, stages, (const R *)mats);
+    return hipGetLastError();
 }
 
 template <class R>
