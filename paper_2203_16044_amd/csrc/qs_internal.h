@@ -203,7 +203,8 @@ struct TileProgram {
     size_t nops = 0;   // operations of the circuit it was formed from
     size_t calls = 0;  // steps that are calls
     std::vector<char> prog;
-    std::vector<TileStep> steps;
+    std::vector<TileStep> steps;  // empty: passes do not pay, every operation is a call
+    double saved_us = 0;          // by the passes
     std::vector<TileOp> open;
     uint64_t open_qubits = 0;
     size_t open_bytes = 0;

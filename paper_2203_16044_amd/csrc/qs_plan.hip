@@ -776,11 +776,14 @@ QS_API int qs_circuit_run(qs_state *st, const qs_circuit *c)
         // qubits complex128, 252 operations 89 us against 176), while calls in between (wide gates, fused-swaps) are
         // launches that LDS saves (48 random operations, half of them calls, 310 us against 234) unless they are
         // complex64, whose 8,192 amplitudes make a wide gate dearer on one compute unit than its launch (400 against 430).
+        bool small = small_eligible(st, c);
         if (qs_tile_fits(st->n, st->dtype))
-            if (const std::shared_ptr<const TileProgram> P = tile_program(c, st->dtype))
-                if (!small_eligible(st, c) || st->dtype == QS_C64 || 8 * P->calls <= c->raw.size())
+            if (const std::shared_ptr<const TileProgram> P = tile_program(c, st->dtype)) {
+                small = small && st->dtype != QS_C64 && 8 * P->calls > c->raw.size();
+                if (!small && !P->steps.empty())
                     return tile_run(st, c, *P);
-        if (small_eligible(st, c))
+            }
+        if (small)
             if (const std::shared_ptr<const SmallProgram> P = small_program(c, st->dtype))
                 return qs_small_run(st, *P);
     }

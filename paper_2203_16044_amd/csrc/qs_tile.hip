@@ -644,20 +644,30 @@ size_t inline_bytes(const TileOp &o, int dtype)
 }
 size_t units_of(const TileOp &o, int dtype) { return 2 + (inline_bytes(o, dtype) + 15) / 16; }
 
-// Microseconds of an operation as a call of its own: a launch, and the share of the lines it reads and rewrites.
+// Microseconds of an operation as a call of its own: its launch or the share of the lines it reads and rewrites, whichever
+// takes longer (dense 2-qubit gates one after the other).
 double call_us(const TileProgram &P, const TileOp &o)
 {
-    return 3.0 + 2e-6 * o.share * (double)(((uint64_t)1 << P.n) * amp_bytes(P.dtype)) / 6.4;
+    const double lines = 2e-6 * o.share * (double)(((uint64_t)1 << P.n) * amp_bytes(P.dtype)) / 6.4;
+    if (o.kind == OP_DENSE2)
+        return 3.0 + lines;
+    return std::max(3.0, 1.0 + lines);
 }
 // ... and of a pass over the whole state with these operations' arithmetic.
 double pass_us(const TileProgram &P, const std::vector<TileOp> &ops)
 {
-    const double amps = (double)((uint64_t)1 << P.n);
-    double us = 6.0 + 2e-6 * amps * amp_bytes(P.dtype) / 5.5;
+    const double amps = (double)((uint64_t)1 << P.n), bytes = amps * amp_bytes(P.dtype);
+    double us = 6.0 + 2e-6 * bytes / (qs_streams((uint64_t)bytes) ? 5.5 : 8.0);
     for (const TileOp &o : ops)
-        us += 0.4 + amps * (o.kind == OP_DENSE2 ? 16 : o.kind == OP_DENSE1 ? 8 : o.kind == OP_DIAGK ? 24 : 4) / 2.2e7;
+        us += (o.kind == OP_DENSE2 ? 1.2 : 0.4) +
+              amps * (o.kind == OP_DENSE2 ? 16 : o.kind == OP_DENSE1 ? 8 : o.kind == OP_DIAGK ? 24 : 4) / 2.2e7;
     return us;
 }
+// The copy of the records in front of the first pass, once a run: what all passes together have to save. Microseconds of
+// a run as passes and as calls, and, waited for, on 16 qubits complex128: 5 U3 gates 14.6 (25.2) and 13.7 (23.6), 6 14.6
+// (25.5) and 16.3 (25.9); dense 2-qubit gates 5 17.3 (27.3) and 15.6 (26.9), 8 22.1 (32.9) and 24.4 (49.5). On 20: 3 U3
+// gates 19.1 and 15.2, 4 20.1 and 21.8.
+constexpr double kUploadUs = 7.0;
 
 void flush(TileProgram &P)
 {
@@ -671,11 +681,13 @@ void flush(TileProgram &P)
     double calls = 0;
     for (const TileOp &o : ops)
         calls += call_us(P, o);
-    if (calls <= pass_us(P, ops)) {
+    const double saved = calls - pass_us(P, ops);
+    if (saved <= 0) {
         for (const TileOp &o : ops)
             P.steps.push_back(TileStep{o.raw, 0, 0, 0, 0});
         return;
     }
+    P.saved_us += saved;
     const int B = tile_bits(P.dtype), LB = line_bits(P.dtype);
     for (int q = 0; __builtin_popcountll(L) < B; ++q)
         L |= (uint64_t)1 << q;
@@ -926,6 +938,10 @@ void qs_tile_finish(TileProgram &P)
     flush(P);
     for (const TileStep &s : P.steps)
         P.calls += s.raw >= 0;
+    if (P.saved_us <= kUploadUs) {
+        P.steps.clear();
+        P.prog.clear();
+    }
 }
 
 namespace {
