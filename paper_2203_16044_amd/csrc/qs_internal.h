@@ -84,6 +84,14 @@ void qs_scratch_drop(qs_state *st);
 // non-temporal (a diagonal gate, complex128: 24 qubits, 256 MiB, 71 us plain against 81; 25 qubits 178 against 163; 27
 // qubits 722 against 649).
 inline bool qs_streams(uint64_t bytes) { return bytes > ((uint64_t)256 << 20); }
+// Whether a gate's pass over a state of `bytes`, in whole lines, is best non-temporal: beyond the last-level cache, and at
+// 16 MiB, half of what the L2s hold together, where plain stores wait in them for the kernel's end. (Sequences of 1-qubit
+// gates, replayed, microseconds a gate plain and non-temporal: 20 qubits complex128 7.1 and 6.3, 21 qubits complex64 9.3
+// and 7.5; half the size 4.2 and 4.2, 5.2 and 5.1; a quarter 3.0 and 3.1; twice the size 8.3 and 10.2, 9.3 and 12.0.)
+inline bool qs_streams_lines(uint64_t bytes)
+{
+    return qs_streams(bytes) || (bytes > ((uint64_t)8 << 20) && bytes <= ((uint64_t)16 << 20));
+}
 
 inline size_t amp_bytes(int dtype) { return dtype == QS_C128 ? 16 : 8; }
 
