@@ -53,7 +53,7 @@ template <class T> __device__ __forceinline__ void st(T *p, T v, int nt)
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// dense k-qubit gate, k <= 3 (and complex128 k = 4 where it streams whole lines, dense_k): the group's 2^k members live in
+// dense k-qubit gate, k <= 3 (and k = 4 where it streams whole lines, dense_k): the group's 2^k members live in
 // registers; U comes from kernel arguments, for k = 4 from device memory through uniform (scalar) loads.
 // ---------------------------------------------------------------------------------------------------------
 template <class R, int K> struct MatByVal {
@@ -893,16 +893,21 @@ hipError_t dense_k(void *psi, uint64_t ngroups, const InsBits &ins, const TPos &
                                (C2 *)psi, ngroups, ins, tp, m, tu.nontemporal);
         }
     } else {
-        // complex128 k = 4 from HBM with no target inside a 128-byte line: groups in registers, which depend less on
-        // where the targets lie than the tiles do (27 qubits, targets 5 9 13 20: 765 us against 929, 4 8 15 24: 763
-        // against 814, 10 12 17 23: 766 against 699; SU(4) layers in 4-qubit blocks 770 against 820 a pass). In cache
-        // (24 qubits: 111 against 95) and with low targets (0 6 11 22: 860 against 743) the tiles are the better form.
-        if constexpr (K == 4 && sizeof(R) == 8)
-            if (qs_streams((ngroups << ins.np) * sizeof(C2)) && tp.tpos[0] >= 3) {
+        // k = 4 from HBM with no target or control inside a 128-byte line: groups in registers, which depend less on where
+        // the targets lie than the tiles do (27 qubits complex128, targets 5 9 13 20: 765 us against 929, 4 8 15 24: 763
+        // against 814, 10 12 17 23: 766 against 699; SU(4) layers in 4-qubit blocks 770 against 820 a pass; complex64,
+        // targets 5 9 10 26: 367 against 402, 4 13 14 26: 366 and 368). In cache (24 qubits complex128: 111 against 95,
+        // complex64 54 and 39), with low targets (0 6 11 22 complex128: 860 against 743) and with low controls (5 13 14 26
+        // controlled by 1: 1157 against 884, complex64 572 against 424) the tiles are the better form.
+        if constexpr (K == 4) {
+            constexpr int line_bits = sizeof(R) == 8 ? 3 : 4;
+            if (qs_streams((ngroups << ins.np) * sizeof(C2)) && tp.tpos[0] >= line_bits &&
+                !(ins.orm & ((1u << line_bits) - 1))) {
                 hipLaunchKernelGGL((k_dense<R, 4, 1, MatByPtr<R>>), dim3(grid_for(ngroups, bs)), dim3(bs), 0, s, (C2 *)psi,
                                    ngroups, ins, tp, MatByPtr<R>{(const R *)Ud}, tu.nontemporal);
                 return hipGetLastError();
             }
+        }
         return launch_dense_mfma(std::is_same<R, double>::value ? QS_C128 : QS_C64, K, psi, ngroups, ins, tp, Ud, s);
     }
     return hipGetLastError();
