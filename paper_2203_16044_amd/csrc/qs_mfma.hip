@@ -13,7 +13,7 @@
 // part), so that its results are theirs bit for bit.
 //
 // Work split: a persistent workgroup of 4 waves walks column tiles of 16 CT consecutive groups, 16 KiB of amplitudes
-// each. Such a tile's amplitudes are the patterns of the targets and of the lowest free qubits, so in address order
+// each (8 on small states). Such a tile's amplitudes are the patterns of the targets and of the lowest free qubits, so in address order
 // they are whole cache lines whichever the targets are: they are loaded and stored in that order, 16 bytes a lane, and
 // find their (member, group) place in LDS by a bit permutation formed once per thread. Each wave keeps its slice of A'
 // in registers for the whole launch. While a tile is multiplied the next one's loads are in flight in registers; the
@@ -311,10 +311,9 @@ hipError_t mfma_p(void *psi, uint64_t ngroups, const InsBits &ins, const TileMap
     return hipGetLastError();
 }
 
-template <class R, int K>
-hipError_t mfma_k(void *psi, uint64_t ngroups, const InsBits &ins, const TPos &tp, const void *U, hipStream_t s)
+template <class R, int K, int CT>
+hipError_t mfma_ct(void *psi, uint64_t ngroups, const InsBits &ins, const TPos &tp, const void *U, hipStream_t s)
 {
-    constexpr int CT = (sizeof(R) == 8 ? 1 : 2) << (6 - K);  // 16 KiB of amplitudes
     constexpr int D = 1 << K, CB = 4 + __builtin_ctz(CT);
     TileMap tm{};
     tm.bits = K + CB;
@@ -349,6 +348,18 @@ hipError_t mfma_k(void *psi, uint64_t ngroups, const InsBits &ins, const TPos &t
         if (!(taken & ~tmask & 1))
             return mfma_p<R, K, CT, true>(psi, ngroups, ins, tm, U, nt, s);
     return mfma_p<R, K, CT, false>(psi, ngroups, ins, tm, U, nt, s);
+}
+
+template <class R, int K>
+hipError_t mfma_k(void *psi, uint64_t ngroups, const InsBits &ins, const TPos &tp, const void *U, hipStream_t s)
+{
+    constexpr int CT = (sizeof(R) == 8 ? 1 : 2) << (6 - K);  // 16 KiB of amplitudes
+    // Fewer tiles than compute units: half as large, since one tile is each workgroup's whole work (16 qubits, k = 6
+    // complex64 9.2 us, so 7.8; k = 5 complex128 5.6 and 4.8).
+    if constexpr (K > 4 && CT > 1)
+        if (ngroups < 16 * CT * (uint64_t)qs_cu_count())
+            return mfma_ct<R, K, CT / 2>(psi, ngroups, ins, tp, U, s);
+    return mfma_ct<R, K, CT>(psi, ngroups, ins, tp, U, s);
 }
 
 }  // namespace
