@@ -1180,17 +1180,22 @@ template <class R> hipError_t fswap_tile(void *psi, int n, int lo, int hi, int s
 
 // Swaps within one line and the lowest bits go tile by tile (from lo on that is a whole line, moving the exchanged runs
 // alone is less; complex128 states streaming from HBM only up to bit 6: 27 qubits, lo 0, s 3, hi 3 1189 us against 789,
-// but s 4, hi 4 725 against 787). Complex64 swaps that leave bit 0 alone move pairs of amplitudes, as complex128 amplitudes of a state of
+// but s 4, hi 4 725 against 787). Where tiles are at most 64 (17 qubits, complex64 18) the wide-row form, whose work items of
+// 2^(hi + s) amplitudes are up to 1024, is faster (16 qubits, lo 0, s 4, hi 4: tiles 2.6 us, rows 2.3, complex64 2.6 and
+// 2.1; with more items the tiles are, 17 qubits, lo 0, s 1, hi 4: 2.7 against 3.4, as with larger ones, lo 1, s 5, hi 6:
+// 2.7 against 4.4). Complex64 swaps that leave bit 0 alone move pairs of amplitudes, as complex128 amplitudes of a state of
 // one qubit less: 16 bytes a lane (27 qubits, lo 1 to 3, hi far above: 510 us, so 380; 25 qubits, in cache, 84 and 65).
 // Whole lines streaming from HBM are the exception: 8 bytes a lane are 5 to 10 % faster (27 qubits, lo 4, s 1: 178 and 195).
 hipError_t launch_fused_swap(int dtype, void *psi, int n, int lo, int hi, int s_, hipStream_t s)
 {
+    const int span = hi + s_;
+    const bool rows = n <= (dtype == QS_C128 ? 17 : 18) && span >= 3 && span <= 9 && n - span <= 10;
     if (dtype == QS_C128)
-        return lo < 3 && hi + s_ <= (qs_streams((uint64_t)16 << n) ? 6 : FswTile<double>::B) && n >= FswTile<double>::B
+        return lo < 3 && span <= (qs_streams((uint64_t)16 << n) ? 6 : FswTile<double>::B) && n >= FswTile<double>::B && !rows
                    ? fswap_tile<double>(psi, n, lo, hi, s_, s)
                    : fswap_t<double2>(psi, n, lo, hi, s_, s);
-    if (lo < 4 && hi + s_ <= FswTile<float>::B && n >= FswTile<float>::B)
-        return fswap_tile<float>(psi, n, lo, hi, s_, s);
+    if (lo < 4 && span <= FswTile<float>::B && n >= FswTile<float>::B)
+        return rows ? fswap_t<float2>(psi, n, lo, hi, s_, s) : fswap_tile<float>(psi, n, lo, hi, s_, s);
     if (lo >= 1 && (lo < 4 || !qs_streams((uint64_t)8 << n)))
         return fswap_t<double2>(psi, n - 1, lo - 1, hi - 1, s_, s);
     return fswap_t<float2>(psi, n, lo, hi, s_, s);
