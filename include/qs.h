@@ -217,9 +217,10 @@ QS_API int qs_circuit_size(const qs_circuit *c, int *nops);
 /* Plain execution: the qs_apply_* / qs_fused_swap calls of the circuit, in order, nothing fused or reordered. Pure moves
  * and unit and -1 diagonal entries stay exact. Unless the stream is being captured (then each operation is a launch of
  * its own), operations share passes over the state:
- *   - Where the state is at most 64 KiB, circuits of 6 operations and more run in one launch that keeps the state in a
- *     compute unit's LDS; results equal the single calls' up to rounding.
- *   - Larger states (from one tile on, 64 KiB) take operations in a row on the qubits of one tile in one pass: gates
+ *   - Where the state has at most 12 qubits, circuits of 6 operations and more run in one launch that keeps the state in
+ *     a compute unit's LDS; results equal the single calls' up to rounding (complex64: bit for bit).
+ *   - Larger states, and 12 qubits complex128 unless more than an eighth of the operations are single calls by the
+ *     following, take operations in a row on the qubits of one 64 KiB tile in one pass: gates
  *     and controlled gates on 1 or 2 targets and diagonals on up to 6, bit for bit the single calls' results. Others,
  *     and runs that would cost less as calls, are single calls.
  * The passes' records go through the state's staging buffer with each run; formed once per circuit and precision, on the

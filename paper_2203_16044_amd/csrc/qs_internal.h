@@ -180,9 +180,11 @@ struct SmallProgram {
     size_t last_dense1 = SIZE_MAX;  // where in it the last record starts, if that is a 1-qubit gate
     std::vector<char> pool;    // larger matrices and tables
 };
-// State bytes up to which a circuit runs that way (128 KiB would fit a CU's LDS; there the passes over tiles are faster:
-// layers of RZ, RX and CNOT on 13 qubits complex128, 252 operations, 383 us against 125 on 14).
-inline size_t qs_small_bytes() { return (size_t)64 << 10; }
+// Qubits up to which a circuit runs that way, four amplitudes a thread. (13 would fit a CU's LDS; there the passes over
+// tiles are faster: layers of RZ, RX and CNOT complex128, 252 operations, 383 us against 125 on 14. Complex64, one tile:
+// 48 random operations, half of them calls between the passes, 430 us against 400, since 8,192 amplitudes make a wide gate
+// dearer on one compute unit than its launch.)
+constexpr int kSmallQubits = 12;
 void qs_small_add_matrix(SmallProgram &P, const int *t, int k, const int *c, int nc, const double *U);
 void qs_small_add_diag(SmallProgram &P, const int *t, int k, const double *d);
 void qs_small_add_swap(SmallProgram &P, int p, int q, int s);

@@ -466,7 +466,7 @@ constexpr size_t kSmallMinOps = 6;
 constexpr size_t kSmallProgramMax = (size_t)2 << 20;  // bytes; the staging ring has 8 MiB
 bool small_eligible(const qs_state *st, const qs_circuit *c)
 {
-    return ((size_t)1 << st->n) * amp_bytes(st->dtype) <= qs_small_bytes() && c->raw.size() >= kSmallMinOps;
+    return st->n <= kSmallQubits && c->raw.size() >= kSmallMinOps;
 }
 bool not_capturing(const qs_state *st)
 {
@@ -772,14 +772,13 @@ QS_API int qs_circuit_run(qs_state *st, const qs_circuit *c)
     if (c->n != st->n)
         return qs_fail(QS_EINVAL, "qs_circuit_run: circuit has %d qubits, state has %d", c->n, st->n);
     if (c->raw.size() > 1 && not_capturing(st)) {
-        // One tile exactly (64 KiB) is one workgroup's work either way, but passes hold the amplitudes in registers (12
-        // qubits complex128, 252 operations 89 us against 176), while calls in between (wide gates, fused-swaps) are
-        // launches that LDS saves (48 random operations, half of them calls, 310 us against 234) unless they are
-        // complex64, whose 8,192 amplitudes make a wide gate dearer on one compute unit than its launch (400 against 430).
+        // One tile exactly (12 qubits complex128) is one workgroup's work either way, but passes hold the amplitudes in
+        // registers (252 operations 89 us against 176), while calls in between (wide gates, fused-swaps) are launches
+        // that LDS saves (48 random operations, half of them calls, 310 us against 234).
         bool small = small_eligible(st, c);
         if (qs_tile_fits(st->n, st->dtype))
             if (const std::shared_ptr<const TileProgram> P = tile_program(c, st->dtype)) {
-                small = small && st->dtype != QS_C64 && 8 * P->calls > c->raw.size();
+                small = small && 8 * P->calls > c->raw.size();
                 if (!small && !P->steps.empty())
                     return tile_run(st, c, *P);
             }

@@ -610,7 +610,7 @@ template <class R, int PER>
 hipError_t launch_per(qs_state *st, uint32_t dim, int nt, const char *prog, uint32_t bytes, const char *pool)
 {
     using C2 = typename ST<R>::C2;
-    if (hipError_t e = qs_allow_lds((const void *)k_small<R, PER>, qs_small_bytes()))
+    if (hipError_t e = qs_allow_lds((const void *)k_small<R, PER>, sizeof(C2) << kSmallQubits))
         return e;
     hipLaunchKernelGGL((k_small<R, PER>), dim3(1), dim3(nt), (size_t)dim * sizeof(C2), st->stream, (C2 *)st->psi, dim,
                        prog, bytes, pool);
@@ -627,7 +627,6 @@ template <class R> hipError_t launch_r(qs_state *st, const char *prog, uint32_t 
     case 1:
     case 2: return launch_per<R, 2>(st, dim, nt, prog, bytes, pool);
     case 4: return launch_per<R, 4>(st, dim, nt, prog, bytes, pool);
-    case 8: return launch_per<R, 8>(st, dim, nt, prog, bytes, pool);
     default: return hipErrorInvalidValue;
     }
 }
