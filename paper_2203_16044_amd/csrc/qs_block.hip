@@ -1573,13 +1573,14 @@ hipError_t batch_b(void *psi, double *probs, const BatchItem *items, int nitems,
     if (nblocks == 0)
         return hipSuccess;
     const uint64_t wgs = (uint64_t)qs_cu_count() * wg_per_cu;  // of 256 threads
-    // Complex128 levels of one 12-qubit block's worth per compute unit and more: the kernel that keeps four workgroups
-    // there. On fewer blocks a stage's three barriers cost more than the company gives (microseconds a batch alone, and
-    // in a stream of three: 8 circuits of 13 to 16 qubits, 10-qubit blocks 464 and 201 against 403 and 176; 6 of 10 to
-    // 18, 11-qubit blocks 352 and 145 against 323 and 134; but 24 of 10 to 20 820 and 444 against 885 and 548). A
-    // threshold of a quarter loses 4 to 14 % on batches up to 19 qubits.
+    // Complex128 levels of one 12-qubit block's worth per compute unit and more, and those of small circuits alone: the
+    // kernel that keeps four workgroups on a compute unit. On fewer blocks of large circuits a stage's three barriers
+    // cost more than the company gives (microseconds a batch alone, and in a stream of three: 8 circuits of 13 to 16
+    // qubits, 10-qubit blocks 464 and 201 against 403 and 176; 6 of 10 to 18, 11-qubit blocks 352 and 145 against 323 and
+    // 134; but 24 of 10 to 20 820 and 444 against 885 and 548, 38 of 9 to 11 190 and 62 against 203 and 65). A threshold
+    // of a quarter loses 4 to 14 % on batches up to 19 qubits.
     if constexpr (sizeof(R) == 8)
-        if (((uint64_t)nblocks << B) >= (uint64_t)qs_cu_count() << 12) {
+        if (((uint64_t)nblocks << B) >= (uint64_t)qs_cu_count() << 12 || (uint32_t)nitems == nblocks) {
             const uint64_t grid = std::min<uint64_t>(wgs << (12 - B), nblocks);
             auto go = [&](auto kernel) {
                 if (hipError_t e = qs_allow_lds((const void *)kernel, (size_t)8 << B))

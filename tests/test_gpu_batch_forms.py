@@ -32,3 +32,19 @@ def test_levels_on_both_sides(gpu, bits, sizes):
                 # at most 60 gates of 4 products and sums each, on probabilities that sum to 1: 60 * 8 half units
                 assert np.max(np.abs(b.probs(i) - w)) <= 1e-12, (sizes[i], wg, graph)
         b.close()
+
+
+@pytest.mark.parametrize("bits", [10, 12])
+def test_levels_that_stream(gpu, bits):
+    """25 qubits, 512 MiB: non-temporal accesses; a small circuit beside it."""
+    circs = [_circ(25, 1025, 12), _circ(9, 1026, 30)]
+    b = Batch(circs, "c128", bits, 3, 32)
+    for graph in (False, True, True):
+        b.run(graph)
+    for i, c in enumerate(circs):
+        psi = np.zeros(1 << c.n, dtype=np.complex128)
+        psi[0] = 1.0
+        for op in c.ops:
+            oracle.apply_op(psi, op)
+        assert np.max(np.abs(b.probs(i) - np.abs(psi) ** 2)) <= 1e-12
+    b.close()
