@@ -400,8 +400,8 @@ QS_API int qs_probe_rmw(void *buf, size_t bytes, void *hip_stream);
  *               default 2; k = 4 takes half of them on states past 256 MiB, complex64 k = 6 half as many again);
  * "block_wg_per_cu" persistent 256-thread workgroups per compute unit of the LDS block kernel (1..4096, default
  *               32: a grid far larger than the resident workgroups measured fastest; smaller workgroups are
- *               scaled up proportionally; complex128 passes of 4 blocks per compute unit and more take a workgroup
- *               per block instead);
+ *               scaled up proportionally). At the default, complex128 passes of 10- to 13-qubit blocks over 2^14
+ *               amplitudes per compute unit and more (22 qubits) run a kernel with a workgroup per block instead;
  * "block_stage_width" register stage width of block plans created afterwards: 4 (256-thread kernel, default) or
  *                     3 (512-thread kernel with 8 register amplitudes per thread, for 12- and 13-qubit blocks);
  * "block_async" 0/1: 12-qubit complex128 block passes double-buffer the next block in LDS with direct-to-LDS loads

@@ -1666,9 +1666,11 @@ hipError_t block_b(void *psi, uint64_t nblocks, const InsBits &outer, const Bloc
     // Four workgroups of 256 threads a CU and more: the kernel that keeps four there. Fewer are a question of latency,
     // and one barrier a stage takes less of it than three (microseconds a pass of SU(4) layers: 12-qubit blocks 20
     // qubits 22.4 against 27.3, 21 qubits 26.7 against 31.5, 22 qubits 50.5 against 47.4, 24 qubits 180 against 174;
-    // 10-qubit blocks 21 qubits 24.2 against 27.4, 22 qubits 42.5 against 41.6).
+    // 10-qubit blocks 21 qubits 24.2 against 27.4, 22 qubits 42.5 against 41.6). A number of workgroups that was asked
+    // for holds: the persistent kernel.
     if constexpr (B >= 10 && W == 4 && sizeof(R) == 8) {
-        if (nblocks << B >= (uint64_t)qs_cu_count() << 14 && !lstages && !qs_tunables().block_async) {
+        if (nblocks << B >= (uint64_t)qs_cu_count() << 14 && !lstages && !qs_tunables().block_async &&
+            qs_tunables().block_wg_per_cu == kBlockWgPerCu) {
             const bool nt = qs_streams((nblocks << B) * 16);
             auto go = [&](auto kernel) {
                 if (hipError_t e = qs_allow_lds((const void *)kernel, (size_t)8 << B))

@@ -360,11 +360,12 @@ template <> struct NT2<float> { typedef float type __attribute__((ext_vector_typ
 
 // tunables (set through qs_set_tunable). Process-wide and atomic: a call on one thread may change them while
 // another thread plans or launches; each launch or plan reads every tunable it uses once.
+constexpr int kBlockWgPerCu = 32;
 struct Tunables {
     std::atomic<int> dense_gpt{1};        // groups per thread for k = 1, 2
     std::atomic<int> nontemporal{1};      // use non-temporal loads/stores in the plain gate kernels
     std::atomic<int> mfma_wg_per_cu{2};   // persistent workgroups per CU for the MFMA block kernel
-    std::atomic<int> block_wg_per_cu{32}; // persistent workgroups per CU for the LDS block kernel (256-thread units)
+    std::atomic<int> block_wg_per_cu{kBlockWgPerCu}; // persistent workgroups per CU for the LDS block kernel (256-thread units)
     std::atomic<int> block_stage_width{4}; // register stage width of new block plans: 4, or 3 (512 threads, b = 12, 13)
     std::atomic<int> plan_beam{16};       // pass formation: beam width over local-set growth (0: fewest-new greedy)
     std::atomic<int> plan_beam_search{0}; // plans (not batches): also 1.5x and 4x that width, fewest passes win

@@ -33,3 +33,31 @@ def test_every_block_size(gpu, n, bits):
         oracle.apply_op(psi, op)
     # 18 operations of at most 8 terms on amplitudes below 0.02
     assert np.max(np.abs(got - psi)) <= 1e-14
+
+
+@pytest.mark.parametrize("bits", [10, 11, 12, 13])
+def test_persistent_workgroups_on_request(gpu, bits):
+    """With block_wg_per_cu set, 22 qubits run the kernel whose workgroups walk several blocks; at its default, the one
+    with a workgroup per block. Both agree with the oracle."""
+    n = 22
+    rng = np.random.Generator(np.random.PCG64(1070))
+    ops = [C.Op("dense", tuple(int(v) for v in rng.permutation(n)[:2]), mat=C._random_unitary(rng, 4)) for _ in range(12)]
+    psi = C.random_state(n, 1071)
+    ref = psi.copy()
+    for op in ops:
+        oracle.apply_op(ref, op)
+    c = Circuit.from_ops(n, ops)
+    p = Plan(c, "block", bits, 3, "c128")
+    st = gpu.State(n, "c128")
+    before = gpu.binding.qs_get_tunable("block_wg_per_cu")
+    try:
+        for wg in (1, 4, before):
+            gpu.binding.qs_set_tunable("block_wg_per_cu", wg)
+            st.set(psi)
+            p.run(st)
+            assert np.max(np.abs(st.get() - ref)) <= 1e-14, wg
+    finally:
+        gpu.binding.qs_set_tunable("block_wg_per_cu", before)
+    p.close()
+    c.close()
+    st.close()
