@@ -396,8 +396,8 @@ QS_API int qs_probe_rmw(void *buf, size_t bytes, void *hip_stream);
 /* ---- launch tunables (autotuner / sweeps) ----
  * "dense_gpt"   groups per thread of the 1- and 2-qubit dense kernels: 1, 2 or 4 (default 1);
  * "nontemporal" 0/1: non-temporal loads and stores in the dense kernels (default 1);
- * "mfma_wg_per_cu" persistent workgroups per compute unit of the k = 5 and complex128 k = 6 MFMA kernels (1..16,
- *               default 2; k = 4 takes half of them on states past 256 MiB, complex64 k = 6 half as many again);
+ * "mfma_wg_per_cu" persistent workgroups per compute unit of the k = 4 to 6 matrix-core kernel (1..16, default 2; at
+ *               most one per tile of amplitudes);
  * "block_wg_per_cu" persistent 256-thread workgroups per compute unit of the LDS block kernel (1..4096, default
  *               32: a grid far larger than the resident workgroups measured fastest; smaller workgroups are
  *               scaled up proportionally). At the default, complex128 passes of 10- to 13-qubit blocks over 2^14
