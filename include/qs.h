@@ -185,17 +185,17 @@ QS_API const char *qs_last_error(void);
  * call takes uniforms in [0, 1), so runs are reproducible and can be checked one by one. */
 /* Measure `qubit`: P0, P1 = FP64 masses with the qubit's bit 0 / 1 (fixed-order reduction), outcome = 1 iff
  * u (P0 + P1) < P1, then the state collapses: amplitudes of the observed outcome are scaled by 1/sqrt(P_outcome)
- * (factor in FP64), the others set to 0. prob_one (nullable) receives P1 / (P0 + P1). Synchronises (the outcome
- * is decided on the host). QS_EINVAL for a qubit out of range, u outside [0, 1) or a state with no finite
+ * (factor in FP64), the others set to 0. prob_one (nullable) receives P1 / (P0 + P1). Waits for the outcome, which
+ * is decided on the device; the collapse may still be running when the call returns. QS_EINVAL for a qubit out of range, u outside [0, 1) or a state with no finite
  * nonzero mass (then the state is unchanged). */
 QS_API int qs_measure(qs_state *st, int qubit, double u, int *outcome, double *prob_one);
 /* Measure `qubit` as qs_measure does, then flip it to |0> if the outcome was 1 (an exact permutation). */
 QS_API int qs_reset(qs_state *st, int qubit, double u, int *outcome);
 /* Draw nshots basis indices (no collapse): shot k returns the smallest i whose cumulative FP64 mass exceeds
- * u[k] x total mass (chunked deterministic prefix sums; every index returned lies in [0, 2^n)). u and out are
- * host arrays of nshots doubles / int64 (0 <= nshots <= 2^30); uses device memory of about 2^(n-11) doubles, and
- * 16 bytes per shot from 32,769 shots on, which the state keeps for its next call when it is at most 64 MiB. Synchronises. QS_EINVAL for u outside [0, 1) or a state with no finite
- * nonzero mass. */
+ * u[k] x total mass (chunked deterministic prefix sums; every index returned lies in [0, 2^n) and has mass). u and
+ * out are host arrays of nshots doubles / int64 (0 <= nshots <= 2^30); uses device memory of about 2^(n-11) doubles,
+ * and 16 bytes per shot from 32,769 shots on, which the state keeps for its next call when it is at most 64 MiB.
+ * Synchronises. QS_EINVAL for u outside [0, 1) or a state with no finite nonzero mass. */
 QS_API int qs_sample(qs_state *st, int64_t nshots, const double *u, int64_t *out);
 
 /* ---- circuits and execution plans ----
@@ -220,9 +220,9 @@ QS_API int qs_circuit_size(const qs_circuit *c, int *nops);
  *   - Where the state has at most 12 qubits, circuits of 6 operations and more run in one launch that keeps the state in
  *     a compute unit's LDS; results equal the single calls' up to rounding (complex64: bit for bit).
  *   - Larger states, and 12 qubits complex128 unless more than an eighth of the operations are single calls by the
- *     following, take operations in a row on the qubits of one 64 KiB tile in one pass: gates
- *     and controlled gates on 1 or 2 targets and diagonals on up to 6, bit for bit the single calls' results. Others,
- *     and runs that would cost less as calls, are single calls.
+ *     following, take operations in a row on the qubits of one 64 KiB tile in one pass: gates and controlled gates
+ *     on 1 or 2 targets and diagonals on up to 6, bit for bit the single calls' results. Others, and runs that would
+ *     cost less as calls, are single calls.
  * The passes' records go through the state's staging buffer with each run; formed once per circuit and precision, on the
  * host. QS_EINVAL if the circuit's qubit count differs from the state's. */
 QS_API int qs_circuit_run(qs_state *st, const qs_circuit *c);

@@ -19,10 +19,11 @@
 // in registers for the whole launch. While a tile is multiplied the next one's loads are in flight in registers; the
 // products go through a second LDS buffer back into address order.
 //
-// What bounds it (27 qubits): HBM for k = 4 and 5 (complex128 0.68 ms = 6.3 TB/s both, complex64 0.36 and 0.34 ms = 6.0
-// and 6.2 TB/s), the matrix cores for k = 6 (complex128 1.14 ms = 60 TFLOP/s, busy 77 % of the cycles at 2.1 GHz;
-// complex64 0.56 ms = 124 TFLOP/s). Tiles of 16 groups with each lane storing its own accumulators took 0.92 and 1.21 ms
-// (k = 5, 6 complex128), 0.65 and 0.73 ms (complex64); the register kernel 0.82-1.35 and 0.38-1.02 ms for k = 4.
+// What bounds it (27 qubits): HBM for k = 4 and 5 (k = 5 complex128 0.68 ms = 6.3 TB/s, complex64 0.34 ms = 6.2 TB/s;
+// k = 4, which from HBM comes here with targets or controls inside a line, 0.74 to 0.87 and 0.37 to 0.43 ms), the matrix
+// cores for k = 6 (complex128 1.14 ms = 60 TFLOP/s, busy 77 % of the cycles at 2.1 GHz; complex64 0.56 ms = 124 TFLOP/s).
+// Tiles of 16 groups with each lane storing its own accumulators took 0.92 and 1.21 ms (k = 5, 6 complex128), 0.65 and
+// 0.73 ms (complex64); the register kernel on those sets for k = 4 0.84-1.34 and 0.42-1.02 ms.
 #include "qs_internal.h"
 
 namespace {

@@ -13,8 +13,9 @@
 //
 // Arithmetic per operation is that of the one-pass kernels, rounding for rounding (1-qubit gates the lane-exchange form
 // takes there in its order, matrix entries otherwise in FMA chains in ascending column order, 5 and 6 targets complex64
-// in the order of the matrix-core tiles), so that complex64 results are the single calls' bit for bit; monomial gates with entries 1, -1, i, -i and fused-swaps are pure moves; diagonal entries 1 leave amplitudes
-// untouched, -1 flips signs.
+// in the order of the matrix-core tiles), so that complex64 results are the single calls' bit for bit; monomial gates
+// with entries 1, -1, i, -i and fused-swaps are pure moves; diagonal entries 1 leave amplitudes untouched, -1 flips
+// signs.
 #include <algorithm>
 #include <cstring>
 

@@ -18,7 +18,7 @@
 // 268 gate by gate, complex64 12.5 against 142; 20 qubits 177 us against 888; 14 qubits 86 us against 448.
 //
 // Operations with more than two targets to mix, and fused-swaps, stay calls of their own, as do runs whose operations
-// together would cost less than a pass.
+// together would cost less than a pass, and whole circuits whose passes save less than the copy of their records costs.
 #include <algorithm>
 #include <cstring>
 
