@@ -39,14 +39,14 @@ FP64_PEAK_TFLOPS = 78.6  # MI355X FP64 vector (= FP64 MFMA): 256 CUs x 4 SIMDs x
 # The readings hold for the kernel sources they were taken on: `sha1` fingerprints those files and the traffic is
 # reported as null once they differ.
 PMC_TRAFFIC = {
-    "block_b12": {"fetch_kib": None, "write_kib": None, "fetch_scale": 2.0, "write_scale": 1.0,
+    "block_b12": {"fetch_kib": 33700661.10, "write_kib": 75767902.39, "fetch_scale": 2.0, "write_scale": 1.0,
                   "sources": ["paper_2203_16044_amd/csrc/qs_block.hip", "paper_2203_16044_amd/csrc/qs_internal.h",
                               "paper_2203_16044_amd/csrc/qs_index.h"],
-                  "sha1": "b3ddcbca772e1ce3187d75f0d5ebf2337aa1b5cf"},
-    "dense_k1": {"fetch_kib": None, "write_kib": None, "fetch_scale": 2.0, "write_scale": 1.0,
+                  "sha1": "a8100eb0b5cb33760aae9dc65b5b89ad912c3ae2"},
+    "dense_k1": {"fetch_kib": 33554446.79, "write_kib": 67110493.54, "fetch_scale": 2.0, "write_scale": 1.0,
                  "sources": ["paper_2203_16044_amd/csrc/qs_kernels.hip", "paper_2203_16044_amd/csrc/qs_internal.h",
                              "paper_2203_16044_amd/csrc/qs_index.h"],
-                 "sha1": "efb0a8143d298d41669494079806e581b2822d18"},
+                 "sha1": "778b571ee3c4c22d6a367e026cf78e53a714b579"},
 }
 
 
