@@ -42,11 +42,11 @@ PMC_TRAFFIC = {
     "block_b12": {"fetch_kib": 33700661.10, "write_kib": 75767902.39, "fetch_scale": 2.0, "write_scale": 1.0,
                   "sources": ["paper_2203_16044_amd/csrc/qs_block.hip", "paper_2203_16044_amd/csrc/qs_internal.h",
                               "paper_2203_16044_amd/csrc/qs_index.h"],
-                  "sha1": "a8100eb0b5cb33760aae9dc65b5b89ad912c3ae2"},
+                  "sha1": "c109e3208e6e9b7578b77a620297a3803d86506b"},
     "dense_k1": {"fetch_kib": 33554446.79, "write_kib": 67110493.54, "fetch_scale": 2.0, "write_scale": 1.0,
                  "sources": ["paper_2203_16044_amd/csrc/qs_kernels.hip", "paper_2203_16044_amd/csrc/qs_internal.h",
                              "paper_2203_16044_amd/csrc/qs_index.h"],
-                 "sha1": "778b571ee3c4c22d6a367e026cf78e53a714b579"},
+                 "sha1": "1b63e2c87ae76154e93e6b5d7130e66cf022908b"},
 }
 
 

@@ -18,6 +18,7 @@
 namespace {
 thread_local std::string g_err;
 constexpr size_t kRingBytes = (size_t)8 << 20;
+constexpr size_t kRunRingBytes = (size_t)4 << 20;  // twice the longest program uploaded at once
 constexpr size_t kHostResultBytes = 4096;
 constexpr int kMaxPartials = 4096;
 }  // namespace
@@ -44,43 +45,62 @@ void qs_clear_error() { g_err.clear(); }
 extern "C" QS_API const char *qs_last_error(void) { return g_err.c_str(); }
 
 // ------------------------------------------------------------------------------------------------------------
-// staging ring: pinned host chunk -> async H2D copy on the state's stream. A host chunk is reused only after
+// staging rings: pinned host chunk -> async H2D copy on the state's stream. A host chunk is reused only after
 // the copy that last read it has completed (event per chunk); device chunk reuse is ordered by the stream.
 // ------------------------------------------------------------------------------------------------------------
 namespace {
 // Reserve `bytes` of the ring, waiting for work that still reads them. use: the chunks they lie in.
-char *ring_reserve(qs_state *st, size_t bytes, RingUse &use)
+char *ring_reserve(StagingRing &r, size_t bytes, RingUse &use)
 {
     const size_t need = (bytes + 255) & ~(size_t)255;
-    if (need > st->ring_bytes) {
-        qs_fail(QS_EINVAL, "staging request of %zu bytes exceeds the %zu-byte ring", bytes, st->ring_bytes);
+    if (need > r.bytes) {
+        qs_fail(QS_EINVAL, "staging request of %zu bytes exceeds the %zu-byte ring", bytes, r.bytes);
         return nullptr;
     }
-    if (st->ring_head + need > st->ring_bytes)
-        st->ring_head = 0;
-    const size_t csz = st->ring_bytes / kRingChunks;
-    use.c0 = (int)(st->ring_head / csz);
-    use.c1 = (int)((st->ring_head + need - 1) / csz);
+    if (r.head + need > r.bytes)
+        r.head = 0;
+    const size_t csz = r.bytes / kRingChunks;
+    use.c0 = (int)(r.head / csz);
+    use.c1 = (int)((r.head + need - 1) / csz);
     for (int c = use.c0; c <= use.c1; ++c) {
-        if (st->ring_ev_live[c]) {
-            hipError_t e = hipEventSynchronize(st->ring_ev[c]);
+        if (r.live[c]) {
+            hipError_t e = hipEventSynchronize(r.ev[c]);
             if (e != hipSuccess) {
                 qs_hip_fail(e, "hipEventSynchronize(staging ring)");
                 return nullptr;
             }
-            st->ring_ev_live[c] = false;
+            r.live[c] = false;
         }
     }
-    char *h = st->hring + st->ring_head;
-    st->ring_head += need;
+    char *h = r.host + r.head;
+    r.head += need;
     return h;
+}
+
+char *ring_upload(StagingRing &r, hipStream_t stream, const char *h, size_t bytes, const RingUse &use)
+{
+    char *d = r.dev + (h - r.host);
+    hipError_t e = hipMemcpyAsync(d, h, bytes, hipMemcpyHostToDevice, stream);
+    if (e != hipSuccess) {
+        qs_hip_fail(e, "hipMemcpyAsync(staging ring)");
+        return nullptr;
+    }
+    for (int c = use.c0; c <= use.c1; ++c) {
+        e = hipEventRecord(r.ev[c], stream);
+        if (e != hipSuccess) {
+            qs_hip_fail(e, "hipEventRecord(staging ring)");
+            return nullptr;
+        }
+        r.live[c] = true;
+    }
+    return d;
 }
 }  // namespace
 
 char *qs_ring_host(qs_state *st, size_t bytes, RingUse *use)
 {
     RingUse u{};
-    char *h = ring_reserve(st, bytes, u);
+    char *h = ring_reserve(st->runs, bytes, u);
     if (use)
         *use = u;
     return h;
@@ -88,31 +108,17 @@ char *qs_ring_host(qs_state *st, size_t bytes, RingUse *use)
 
 char *qs_ring_upload(qs_state *st, const char *h, size_t bytes, const RingUse &use)
 {
-    char *d = st->dring + (h - st->hring);
-    hipError_t e = hipMemcpyAsync(d, h, bytes, hipMemcpyHostToDevice, st->stream);
-    if (e != hipSuccess) {
-        qs_hip_fail(e, "hipMemcpyAsync(staging ring)");
-        return nullptr;
-    }
-    for (int c = use.c0; c <= use.c1; ++c) {
-        e = hipEventRecord(st->ring_ev[c], st->stream);
-        if (e != hipSuccess) {
-            qs_hip_fail(e, "hipEventRecord(staging ring)");
-            return nullptr;
-        }
-        st->ring_ev_live[c] = true;
-    }
-    return d;
+    return ring_upload(st->runs, st->stream, h, bytes, use);
 }
 
 void *qs_stage(qs_state *st, const void *host, size_t bytes)
 {
     RingUse use;
-    char *h = ring_reserve(st, bytes, use);
+    char *h = ring_reserve(st->gates, bytes, use);
     if (!h)
         return nullptr;
     std::memcpy(h, host, bytes);
-    return qs_ring_upload(st, h, bytes, use);
+    return ring_upload(st->gates, st->stream, h, bytes, use);
 }
 
 char *qs_scratch(qs_state *st, size_t bytes)
@@ -324,15 +330,16 @@ void release(qs_state *st)
         return;
     if (st->stream || st->psi)
         (void)hipStreamSynchronize(st->stream);
-    for (int c = 0; c < kRingChunks; ++c)
-        if (st->ring_ev[c])
-            (void)hipEventDestroy(st->ring_ev[c]);
+    for (StagingRing *r : {&st->gates, &st->runs})
+        for (hipEvent_t ev : r->ev)
+            if (ev)
+                (void)hipEventDestroy(ev);
     if (st->hresult_ev)
         (void)hipEventDestroy(st->hresult_ev);
-    if (st->hring)
-        (void)hipHostFree(st->hring);
-    if (st->dring)
-        (void)hipFree(st->dring);
+    if (st->gates.host)  // one allocation with the runs' ring
+        (void)hipHostFree(st->gates.host);
+    if (st->gates.dev)
+        (void)hipFree(st->gates.dev);
     if (st->red)
         (void)hipFree(st->red);
     if (st->blkred)
@@ -630,34 +637,38 @@ QS_API int qs_alloc(qs_state **out, int n, int dtype, void *dev_buf, void *hip_s
         }
         st->owns = true;
     }
-    st->ring_bytes = kRingBytes;
-    e = hipHostMalloc((void **)&st->hring, kRingBytes + kHostResultBytes, hipHostMallocDefault);
+    st->gates.bytes = kRingBytes;
+    st->runs.bytes = kRunRingBytes;
+    e = hipHostMalloc((void **)&st->gates.host, kRingBytes + kRunRingBytes + kHostResultBytes, hipHostMallocDefault);
     if (e != hipSuccess) {
-        st->hring = nullptr;
+        st->gates.host = nullptr;
         rc = qs_hip_fail(e, "hipHostMalloc(staging ring)");
         goto fail;
     }
-    st->hresult = reinterpret_cast<double *>(st->hring + kRingBytes);
+    st->runs.host = st->gates.host + kRingBytes;
+    st->hresult = reinterpret_cast<double *>(st->runs.host + kRunRingBytes);
     e = hipEventCreateWithFlags(&st->hresult_ev, hipEventDisableTiming);
     if (e != hipSuccess) {
         st->hresult_ev = nullptr;
         rc = qs_hip_fail(e, "hipEventCreate");
         goto fail;
     }
-    e = hipMalloc((void **)&st->dring, kRingBytes);
+    e = hipMalloc((void **)&st->gates.dev, kRingBytes + kRunRingBytes);
     if (e != hipSuccess) {
-        st->dring = nullptr;
+        st->gates.dev = nullptr;
         rc = qs_hip_fail(e, "hipMalloc(staging ring)");
         goto fail;
     }
-    for (int c = 0; c < kRingChunks; ++c) {
-        e = hipEventCreateWithFlags(&st->ring_ev[c], hipEventDisableTiming);
-        if (e != hipSuccess) {
-            st->ring_ev[c] = nullptr;
-            rc = qs_hip_fail(e, "hipEventCreate");
-            goto fail;
+    st->runs.dev = st->gates.dev + kRingBytes;
+    for (StagingRing *r : {&st->gates, &st->runs})
+        for (hipEvent_t &ev : r->ev) {
+            e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+            if (e != hipSuccess) {
+                ev = nullptr;
+                rc = qs_hip_fail(e, "hipEventCreate");
+                goto fail;
+            }
         }
-    }
     st->red_cap = kMaxPartials + 8;
     e = hipMalloc((void **)&st->red, st->red_cap * sizeof(double));
     if (e != hipSuccess) {

@@ -30,6 +30,16 @@ void qs_clear_error();
 // ------------------------------------------------------------------------------------------------------------
 constexpr int kRingChunks = 16;
 
+// Pinned host memory and as much device memory, taken in turn: what a kernel reads that does not fit its arguments.
+struct StagingRing {
+    char *host = nullptr;
+    char *dev = nullptr;
+    size_t bytes = 0;
+    size_t head = 0;
+    hipEvent_t ev[kRingChunks] = {};  // after the last copy from a chunk
+    bool live[kRingChunks] = {};
+};
+
 struct qs_state {
     int n = 0;
     int dtype = QS_C128;
@@ -37,13 +47,11 @@ struct qs_state {
     void *psi = nullptr;
     bool owns = false;
     hipStream_t stream = nullptr;
-    // staging ring for matrices / tables that do not fit in kernel arguments: pinned host + device
-    char *hring = nullptr;
-    char *dring = nullptr;
-    size_t ring_bytes = 0;
-    size_t ring_head = 0;
-    hipEvent_t ring_ev[kRingChunks] = {};
-    bool ring_ev_live[kRingChunks] = {};
+    // Matrices and tables of single gates, which may be captured: a graph reads them from the ring's host memory at
+    // each replay, and an event of an earlier copy cannot be waited for while capturing. So what is never captured, the
+    // programs of plain runs and the shots of qs_sample, has a ring of its own.
+    StagingRing gates;
+    StagingRing runs;
     // FP64 reduction scratch: per-block partial sums followed by the result slot, the pending-norm slot and a
     // measurement's result
     double *red = nullptr;
@@ -64,10 +72,10 @@ double *qs_pending_norm(qs_state *st);
 // recorded on failure)
 double *qs_block_partials(qs_state *st, size_t n);
 
-// Copy `bytes` of host data to the device through the staging ring (async on st->stream). Returns the device
+// Copy `bytes` of host data to the device through the gates' staging ring (async on st->stream). Returns the device
 // address, or nullptr on failure (error already recorded).
 void *qs_stage(qs_state *st, const void *host, size_t bytes);
-// `bytes` of the ring's pinned host memory that no copy still reads (nullptr and the error recorded on failure). The
+// `bytes` of the runs' ring, pinned host memory that no copy still reads (nullptr and the error recorded on failure). The
 // caller waits for its own use of them before it returns, or fills them and has qs_ring_upload copy them to the device
 // (async on st->stream; returns the device address, or nullptr and the error recorded).
 struct RingUse {
@@ -206,7 +214,6 @@ struct TileStep {
     int raw;          // an operation run as a call, or -1: a pass
     uint64_t qubits;  // of the tile
     size_t at, bytes; // its records
-    size_t staged;    // a call: bytes it takes of the staging ring
 };
 struct TileProgram {
     int dtype = QS_C128, n = 0;
@@ -222,7 +229,7 @@ struct TileProgram {
 bool qs_tile_fits(int n, int dtype);
 void qs_tile_add_matrix(TileProgram &P, int raw, const int *t, int k, const int *c, int nc, const double *U);
 void qs_tile_add_diag(TileProgram &P, int raw, const int *t, int k, const double *d);
-void qs_tile_add_call(TileProgram &P, int raw, size_t staged);
+void qs_tile_add_call(TileProgram &P, int raw);
 void qs_tile_finish(TileProgram &P);
 int qs_tile_upload(qs_state *st, const TileProgram &P, size_t i, size_t *end, const char **dev);
 int qs_tile_pass(qs_state *st, const TileStep &step, const char *dev);

@@ -461,9 +461,9 @@ int run_raw(qs_state *st, const RawOp &r)
 // Whether a plain run of circuit c on st can go as one launch over LDS (qs_small.hip): the state fits, and there are
 // operations enough that one launch and the copy of its program (13 us in a stream of runs, 21 us alone) beat a launch
 // each (6 operations: 17-24 and 27-29 us; 4 operations: 11-13 and 22-24).
-// Not under stream capture: a replayed graph would read the program from the staging ring after it has been reused.
+// Not under stream capture: a replayed graph would read the program from the runs' ring after it has been reused.
 constexpr size_t kSmallMinOps = 6;
-constexpr size_t kSmallProgramMax = (size_t)2 << 20;  // bytes; the staging ring has 8 MiB
+constexpr size_t kSmallProgramMax = (size_t)2 << 20;  // bytes; the runs' ring has 4 MiB
 bool small_eligible(const qs_state *st, const qs_circuit *c)
 {
     return st->n <= kSmallQubits && c->raw.size() >= kSmallMinOps;
@@ -490,7 +490,7 @@ try {
         for (size_t i = 0; i < c->raw.size(); ++i) {
             const RawOp &r = c->raw[i];
             if (r.kind == 3)
-                qs_tile_add_call(*P, (int)i, 0);
+                qs_tile_add_call(*P, (int)i);
             else if (r.kind == 1)
                 qs_tile_add_diag(*P, (int)i, r.t.data(), (int)r.t.size(), r.m.data());
             else
@@ -519,7 +519,7 @@ int tile_run(qs_state *st, const qs_circuit *c, const TileProgram &P)
     return QS_OK;
 }
 
-// The circuit's program, or null if it is too long for the staging ring or does not fit host memory.
+// The circuit's program, or null if it is too long for the runs' ring or does not fit host memory.
 std::shared_ptr<const SmallProgram> small_program(const qs_circuit *c, int dtype)
 try {
     std::lock_guard<std::mutex> lock(c->small_mu);

@@ -9,7 +9,7 @@
 // The circuit travels as a program: records of 32 bytes, those of 1- and 2-qubit gates followed by their matrix, packed
 // into 8 KiB chunks that the kernel brings into the scalar cache one at a time; larger matrices and tables lie in a
 // pool behind them. The program is formed once per circuit and precision, on the host, and goes to the device through
-// the state's staging ring with each run.
+// the runs' ring of the state with each run.
 //
 // Arithmetic per operation is that of the one-pass kernels, rounding for rounding (1-qubit gates the lane-exchange form
 // takes there in its order, matrix entries otherwise in FMA chains in ascending column order, 5 and 6 targets complex64

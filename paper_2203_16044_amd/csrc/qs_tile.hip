@@ -56,7 +56,7 @@ struct Rec {
 static_assert(sizeof(Rec) == 32, "program record");
 constexpr size_t kTail = sizeof(Rec) + 64;     // what a pass's records end with: a record, read as if a matrix followed
 constexpr size_t kPassBytes = 12288;           // of records: of a 16 KiB scalar cache
-constexpr size_t kSlabBytes = (size_t)2 << 20; // of programs and other staging between an upload and its last use
+constexpr size_t kSlabBytes = (size_t)2 << 20; // of records uploaded at once: half the ring they go through
 
 template <class R> struct TT;
 template <> struct TT<double> {
@@ -684,7 +684,7 @@ void flush(TileProgram &P)
     const double saved = calls - pass_us(P, ops);
     if (saved <= 0) {
         for (const TileOp &o : ops)
-            P.steps.push_back(TileStep{o.raw, 0, 0, 0, 0});
+            P.steps.push_back(TileStep{o.raw, 0, 0, 0});
         return;
     }
     P.saved_us += saved;
@@ -799,7 +799,7 @@ void flush(TileProgram &P)
     emit(Rec{}, kTail - sizeof(Rec));  // OP_END
     while (P.prog.size() % 64)
         P.prog.resize(P.prog.size() + 16, 0);
-    P.steps.push_back(TileStep{-1, L, at, P.prog.size() - at, 0});
+    P.steps.push_back(TileStep{-1, L, at, P.prog.size() - at});
 }
 
 void add(TileProgram &P, TileOp &&o)
@@ -873,16 +873,16 @@ void add_diag(TileProgram &P, int raw, const int *t, int k, const double *d)
 
 bool qs_tile_fits(int n, int dtype) { return n >= tile_bits(dtype); }
 
-void qs_tile_add_call(TileProgram &P, int raw, size_t staged)
+void qs_tile_add_call(TileProgram &P, int raw)
 {
     flush(P);
-    P.steps.push_back(TileStep{raw, 0, 0, 0, staged});
+    P.steps.push_back(TileStep{raw, 0, 0, 0});
 }
 
 void qs_tile_add_diag(TileProgram &P, int raw, const int *t, int k, const double *d)
 {
     if (k > 6) {  // the records are to fit the scalar cache
-        qs_tile_add_call(P, raw, (amp_bytes(P.dtype) + 1) << k);
+        qs_tile_add_call(P, raw);
         return;
     }
     add_diag(P, raw, t, k, d);
@@ -901,7 +901,7 @@ void qs_tile_add_matrix(TileProgram &P, int raw, const int *t, int k, const int 
         return;
     }
     if (k > 2) {
-        qs_tile_add_call(P, raw, amp_bytes(P.dtype) << (2 * k));
+        qs_tile_add_call(P, raw);
         return;
     }
     TPos tp{};
@@ -974,15 +974,14 @@ template <class R> hipError_t launch_tile(qs_state *st, const TileStep &step, co
 }
 }  // namespace
 
-// Upload the records of as many passes from step `i` on as may lie in the ring until their turn, with what the calls
-// between them stage there; `end` receives the first step beyond.
+// Upload the records of as many passes from step `i` on as make a slab; `end` receives the first step beyond.
 int qs_tile_upload(qs_state *st, const TileProgram &P, size_t i, size_t *end, const char **dev)
 {
     size_t total = 0, lo = 0, hi = 0;
     size_t j = i;
     for (; j < P.steps.size(); ++j) {
         const TileStep &s = P.steps[j];
-        const size_t more = s.raw < 0 ? s.bytes : s.staged + 4096;
+        const size_t more = s.raw < 0 ? s.bytes : 0;
         if (total && total + more > kSlabBytes)
             break;
         total += more;
